@@ -184,9 +184,8 @@ __device__ __forceinline__ void kick_block(Lane& L, const Exch<G, EXCH>& ex, dou
   if (GR) {
     ex.momentum(L.m, L.vx, L.vy, L.vz, sx, sy, sz);
     double k1 = ta * inv_m0;
-    double dqx = k1 * sx, dqy = k1 * sy, dqz = k1 * sz;
-    L.cqx += dqx; L.cqy += dqy; L.cqz += dqz;
-    double qx = L.qx + dqx, qy = L.qy + dqy, qz = L.qz + dqz;
+    L.cqx = fma(k1, sx, L.cqx); L.cqy = fma(k1, sy, L.cqy); L.cqz = fma(k1, sz, L.cqz);
+    const double qx = fma(k1, sx, L.qx), qy = fma(k1, sy, L.qy), qz = fma(k1, sz, L.qz);
     ex.accel(qx, qy, qz, L.m, ax, ay, az);
     double gx, gy, gz;
     gr_accel(qx, qy, qz, kg, gx, gy, gz);
@@ -194,12 +193,11 @@ __device__ __forceinline__ void kick_block(Lane& L, const Exch<G, EXCH>& ex, dou
   } else {
     ex.accel(L.qx, L.qy, L.qz, L.m, ax, ay, az);
   }
-  double dvx = ti * ax, dvy = ti * ay, dvz = ti * az;
-  L.cvx += dvx; L.cvy += dvy; L.cvz += dvz;
-  vkx = L.vx + dvx; vky = L.vy + dvy; vkz = L.vz + dvz;
+  L.cvx = fma(ti, ax, L.cvx); L.cvy = fma(ti, ay, L.cvy); L.cvz = fma(ti, az, L.cvz);
+  vkx = fma(ti, ax, L.vx); vky = fma(ti, ay, L.vy); vkz = fma(ti, az, L.vz);
   ex.momentum(L.m, vkx, vky, vkz, sx, sy, sz);
   double k2 = (GR ? tc : ta + tc) * inv_m0;
-  L.cqx += k2 * sx; L.cqy += k2 * sy; L.cqz += k2 * sz;
+  L.cqx = fma(k2, sx, L.cqx); L.cqy = fma(k2, sy, L.cqy); L.cqz = fma(k2, sz, L.cqz);
   renorm_all(L);
 }
 
@@ -347,19 +345,20 @@ __device__ __forceinline__ void step_lane(const StepParams& p, Lane& L, int lane
     JacConst jc{0.0, 0.0, 0.0, 0.0};
     if constexpr (JAC) jc = jac_const<G>(L.m0, L.m, pg);
     const double mu = JAC ? jc.Mi : L.m0;
+    // One loop over the n K-B units of a step; unrolled by k, the kernel
+    // held several copies of the body and a register set for each path.
     const double c1dt = p.sc[0] * dt;
+    const double sc1 = p.sc[1], sc2 = p.sc[2], sc3 = p.sc[3], sd0 = p.sd[0], sd1 = p.sd[1], sd2 = p.sd[2], sd3 = p.sd[3];
     double tk = L.first ? c1dt : 2.0 * c1dt;
-    for (int s = 0; s < p.n_steps; ++s) {
-      drift(L, mu, tk, dg);
-      tk = 2.0 * c1dt;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (k < p.saba_n) {
-          const double tb = p.sd[k] * dt;
-          if constexpr (JAC) kick_jacobi<G, EXCH, GR>(L, ex, jc, pg, tb, vkx, vky, vkz, kg);
-          else kick_block<G, false, EXCH>(L, ex, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vkx, vky, vkz);
-          if (k + 1 < p.saba_n) drift(L, mu, p.sc[k + 1] * dt, dg);
-        }
+    const int n_units = p.saba_n, n_steps = p.n_steps;
+    for (int s = 0; s < n_steps; ++s) {
+#pragma unroll 1
+      for (int k = 0; k < n_units; ++k) {
+        drift(L, mu, tk, dg);
+        const double tb = (k == 0 ? sd0 : k == 1 ? sd1 : k == 2 ? sd2 : sd3) * dt;
+        if constexpr (JAC) kick_jacobi<G, EXCH, GR>(L, ex, jc, pg, tb, vkx, vky, vkz, kg);
+        else kick_block<G, false, EXCH>(L, ex, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vkx, vky, vkz);
+        tk = k + 1 < n_units ? (k == 0 ? sc1 : k == 1 ? sc2 : sc3) * dt : 2.0 * c1dt;
       }
     }
   } else if constexpr (JAC) {
@@ -397,14 +396,7 @@ __device__ __forceinline__ void step_lane(const StepParams& p, Lane& L, int lane
       drift<KC>(L, L.m0, dt, dg);
     }
   }
-  int f = 0;
-  if (L.pl >= 0) {
-    bool fin = __builtin_isfinite(L.qx) && __builtin_isfinite(L.qy) && __builtin_isfinite(L.qz) &&
-               __builtin_isfinite(L.vx) && __builtin_isfinite(L.vy) && __builtin_isfinite(L.vz);
-    if (!fin) f |= WH_F_NONFINITE;
-    if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
-    if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
-  }
+  int f = lane_flags(L, dg, p.zlim);
   f = group_or<G>(f);
   if ((lane & (G - 1)) == 0 && L.sys >= 0) {
     p.flags[L.sys] |= (uint32_t)f;
@@ -799,7 +791,7 @@ __device__ void apply_corrector(const StepParams& p, Lane& L, int lane, bool inv
   Exch<G, 0> ex;
   ex.init(lane, L.m);
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepDiag dg{0.0, 1.0e300};
+  KepNoDiag dg;
   double vkx, vky, vkz;
   const double h = L.dt;
 #pragma unroll
@@ -839,7 +831,7 @@ __device__ void corrector_run(const StepParams& p, Lane& L, int lane, bool inver
   Exch<G, 0> ex;
   ex.init(lane, L.m);
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepDiag dg{0.0, 1.0e300};
+  KepNoDiag dg;
   double vkx, vky, vkz;
   for (int j = 0; j < n_sub; ++j) {
     double tau;
@@ -854,7 +846,7 @@ __device__ void sync_lane(const StepParams& p, Lane& L, int lane) {
   if (!L.first) {   // uniform over the group: one system, one flag
     const double h = 0.5 * L.dt;
     if (SCHEME == WH_DKD || SCHEME == SCHEME_SABA) {
-      KepDiag dg{0.0, 1.0e300};
+      KepNoDiag dg;
       const double tau = SCHEME == SCHEME_SABA ? p.sc[0] * L.dt : h;
       double mu = L.m0;
       if constexpr (JAC) mu = jac_const<G>(L.m0, L.m, pg).Mi;
@@ -1000,7 +992,7 @@ template <bool GR, int SCHEME> __device__ void sync_group_mixed(const SyncParams
   if (!L.first) {
     const double h = 0.5 * L.dt;
     if (SCHEME == WH_DKD) {
-      KepDiag dg{0.0, 1.0e300};
+      KepNoDiag dg;
       drift(L, L.m0, h, dg);
     } else {
       double vkx, vky, vkz;
@@ -1113,7 +1105,7 @@ template <int G, bool GR, int SCHEME> __device__ void sync_group_pair(const Sync
   if (!A.first) {
     const double h = 0.5 * A.dt;
     if (SCHEME == WH_DKD || SCHEME == SCHEME_SABA) {
-      KepDiag dg{0.0, 1.0e300};
+      KepNoDiag dg;
       const double tau = SCHEME == SCHEME_SABA ? p.sc[0] * A.dt : h;
       drift(A, A.m0, tau, dg);
       drift(B, B.m0, tau, dg);
@@ -1342,7 +1334,7 @@ __device__ void adj_record_lane(const AdjParams& q, int slot, int lane) {
   const double dt = L.dt, h = 0.5 * dt;
   const double inv_m0 = 1.0 / L.m0;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepDiag dg{0.0, 1.0e300};
+  KepNoDiag dg;
   if constexpr (SCH == SCHEME_SABA) {
     // SABA_n: n units per step, unit k = K(tau_k) then the perturbation kick
     // B(d_k dt); tau_0 = c_1 dt (2 c_1 dt after the first step), tau_k = c_{k+1} dt
@@ -1585,7 +1577,7 @@ __device__ void adj_record_pair(const AdjParams& q, int sa) {
   const double dt = p.dts[sa], h = 0.5 * dt;
   const double inv_m0 = 1.0 / A.m0;
   const double kg = GR ? p.kgr * A.m0 * A.m0 : 0.0;
-  KepDiag dga{0.0, 1.0e300}, dgb{0.0, 1.0e300};
+  KepNoDiag dga, dgb;
   if constexpr (SCH == SCHEME_SABA) {
     const int nu = p.saba_n;
     const double c1dt = p.sc[0] * dt;
@@ -2161,7 +2153,7 @@ __device__ void adj_record_jac(const AdjParams& q, int slot, int lane) {
   const JacConst jc = jac_const<G>(L.m0, L.m, pg);
   const double dt = p.dts[slot], h = 0.5 * dt;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepDiag dg{0.0, 1.0e300};
+  KepNoDiag dg;
   auto put_state = [&](double* row) {
     row[0] = L.qx; row[ns] = L.qy; row[2 * ns] = L.qz;
     row[3 * ns] = L.vx; row[4 * ns] = L.vy; row[5 * ns] = L.vz;
@@ -2308,7 +2300,7 @@ __device__ void corrector_vjp(const StepParams& p, const Lane& L0, int lane, boo
     double tau;
     if (corrector_substep(p, j, inverse, L0.dt, tau)) {
       Lane Lx = L;
-      KepDiag dg{0.0, 1.0e300};
+      KepNoDiag dg;
       const double X = drift(Lx, jc.Mi, tau, dg);
       KepFwd k;
       jac_drift_vjp(a, gMim1, jc.Mi, L.qx, L.qy, L.qz, L.vx, L.vy, L.vz, tau, X, k);
@@ -2343,7 +2335,7 @@ template <int G, bool GR, int SCH> __device__ void adj_init_jac_lane(const AdjPa
   const double x0x = L.qx, x0y = L.qy, x0z = L.qz, v0x = L.vx, v0y = L.vy, v0z = L.vz;
   double tau = 0.0, X = 0.0;
   if (!synced) {
-    KepDiag dg{0.0, 1.0e300};
+    KepNoDiag dg;
     if (SCH == WH_KDK) {
       double vkx, vky, vkz;
       kick_jacobi<G, 1, GR>(L, ex, jc, pg, 0.5 * dt, vkx, vky, vkz, kg);
@@ -2444,7 +2436,7 @@ __global__ void k_adj_init(AdjParams q, int synced) {
       double vx = q.ck[3 * ns + slot], vy = q.ck[4 * ns + slot], vz = q.ck[5 * ns + slot];
       // the pending drift: K(dt/2), or K(c_1 dt) for SABA_n
       double m0 = p.m0s[slot], h = p.saba_n > 0 ? p.sc[0] * p.dts[slot] : 0.5 * p.dts[slot];
-      KepDiag dg{0.0, 1.0e300};
+      KepNoDiag dg;
       KepCoef kc;
       double X = kepler_coeffs<KEP_NH, KEP_NN, KEP_KH, KEP_KN>(qx, qy, qz, vx, vy, vz, m0, h, dg, kc);
       KepFwd k;
