@@ -211,6 +211,7 @@ __device__ __forceinline__ void kick_block(Lane& L, const Exch<G, EXCH>& ex, dou
 //   h_i = x'_i + sum_{j<i} w_j x'_j.
 struct JacConst {
   double Mi, inv_Mim1, w, ratio;   // ratio = m0 / M_{i-1} (exactly 1 for the innermost planet)
+  double inv_Mi, inv_m0;           // for the adjoint
 };
 template <int G> __device__ __forceinline__ JacConst jac_const(double m0, double m, int p) {
   JacConst c;
@@ -219,6 +220,8 @@ template <int G> __device__ __forceinline__ JacConst jac_const(double m0, double
   c.inv_Mim1 = 1.0 / Mim1;
   c.w = m / c.Mi;
   c.ratio = m0 / Mim1;
+  c.inv_Mi = 1.0 / c.Mi;
+  c.inv_m0 = 1.0 / m0;
   return c;
 }
 template <int G> __device__ __forceinline__ double jac_to_helio(double x, double w, int p) {
@@ -342,7 +345,7 @@ __device__ __forceinline__ void step_lane(const StepParams& p, Lane& L, int lane
     // B is the whole perturbation: I and J together in DHC (their flows
     // commute without GR), the Jacobi kick in Jacobi coordinates.
     const int pg = lane & (G - 1);
-    JacConst jc{0.0, 0.0, 0.0, 0.0};
+    JacConst jc{};
     if constexpr (JAC) jc = jac_const<G>(L.m0, L.m, pg);
     const double mu = JAC ? jc.Mi : L.m0;
     // One loop over the n K-B units of a step; unrolled by k, the kernel
@@ -1249,33 +1252,37 @@ __device__ __forceinline__ void store_grad(double* g, int ns, int slot, const Gr
   g[6 * ns + slot] = a.m; g[7 * ns + slot] = a.m0;
 }
 
-// Adjoint of the jump Q += kj sum_j m_j V_j (kj = tau/m0) given the group's
-// momentum S = sum_j m_j V_j: gV_i += kj m_i sum_k gQ_k, gm_i += kj V_i .
-// sum_k gQ_k, and gm0 gets -(kj/m0) S . sum_k gQ_k once per group.
-template <int G>
-__device__ __forceinline__ void jump_vjp(Grad& a, double m, double vx, double vy, double vz, double kj, double m0,
-                                         double sx, double sy, double sz, bool leader) {
-  double Gx = group_sum<G>(a.qx), Gy = group_sum<G>(a.qy), Gz = group_sum<G>(a.qz);
-  double km = kj * m;
+// Adjoint of the jump Q += kj sum_j m_j V_j (kj = tau/m0, inv_m0 = 1/m0):
+// gV_i += kj m_i sum_k gQ_k, gm_i += kj V_i . sum_k gQ_k, and
+// gm0 -= (kj/m0) (sum_j m_j V_j) . sum_k gQ_k.  Each lane adds its own
+// planet's term of the last one to its share of gm0 (the shares are summed
+// at the end), so the sum of the momenta is not formed: three group sums
+// fewer per step than with the whole product on one lane of the group.
+__device__ __forceinline__ void jump_vjp_planet(Grad& a, double m, double vx, double vy, double vz, double kj,
+                                                double inv_m0, double Gx, double Gy, double Gz) {
+  const double km = kj * m;
   a.vx = fma(km, Gx, a.vx);
   a.vy = fma(km, Gy, a.vy);
   a.vz = fma(km, Gz, a.vz);
-  a.m += kj * (vx * Gx + vy * Gy + vz * Gz);
-  if (leader) a.m0 -= kj / m0 * (sx * Gx + sy * Gy + sz * Gz);
+  const double t = kj * (vx * Gx + vy * Gy + vz * Gz);
+  a.m += t;
+  a.m0 -= inv_m0 * m * t;
+}
+template <int G>
+__device__ __forceinline__ void jump_vjp(Grad& a, double m, double vx, double vy, double vz, double kj,
+                                         double inv_m0) {
+  const double Gx = group_sum<G>(a.qx), Gy = group_sum<G>(a.qy), Gz = group_sum<G>(a.qz);
+  jump_vjp_planet(a, m, vx, vy, vz, kj, inv_m0, Gx, Gy, Gz);
 }
 
 // The jump adjoint in the pair layout: the sums run over both slots of the
 // group's lanes.
 template <int G>
 __device__ __forceinline__ void jump_vjp_pair(Grad& a, Grad& b, double ma, double mb, const double va[3],
-                                              const double vb[3], double kj, double m0, const double sm[3],
-                                              bool leader) {
+                                              const double vb[3], double kj, double inv_m0) {
   const double Gx = group_sum<G>(a.qx + b.qx), Gy = group_sum<G>(a.qy + b.qy), Gz = group_sum<G>(a.qz + b.qz);
-  a.vx = fma(kj * ma, Gx, a.vx); a.vy = fma(kj * ma, Gy, a.vy); a.vz = fma(kj * ma, Gz, a.vz);
-  b.vx = fma(kj * mb, Gx, b.vx); b.vy = fma(kj * mb, Gy, b.vy); b.vz = fma(kj * mb, Gz, b.vz);
-  a.m += kj * (va[0] * Gx + va[1] * Gy + va[2] * Gz);
-  b.m += kj * (vb[0] * Gx + vb[1] * Gy + vb[2] * Gz);
-  if (leader) a.m0 -= kj / m0 * (sm[0] * Gx + sm[1] * Gy + sm[2] * Gz);
+  jump_vjp_planet(a, ma, va[0], va[1], va[2], kj, inv_m0, Gx, Gy, Gz);
+  jump_vjp_planet(b, mb, vb[0], vb[1], vb[2], kj, inv_m0, Gx, Gy, Gz);
 }
 
 // Adjoint of the interaction kick with the exchange the forward kick used.
@@ -1291,26 +1298,23 @@ __device__ __forceinline__ void interaction_vjp(const Exch<G, 1>& ex, double qx,
 // without GR) at the forward point (Q0, V0), with vk the velocity after the
 // kick: a holds dL/d(output) and receives dL/d(input).
 template <int G, bool GR>
-__device__ __forceinline__ void kick_block_vjp(Grad& a, const Exch<G, 1>& ex, double m, double m0, double inv_m0,
+__device__ __forceinline__ void kick_block_vjp(Grad& a, const Exch<G, 1>& ex, double m, double inv_m0,
                                                double kg, double q0x, double q0y, double q0z, double v0x, double v0y,
                                                double v0z, double vkx, double vky, double vkz, double ta, double ti,
-                                               double tc, bool leader) {
+                                               double tc) {
   if (GR) {
-    double s1x, s1y, s1z, s3x, s3y, s3z;
+    double s1x, s1y, s1z;
     group_momentum<G>(m, v0x, v0y, v0z, s1x, s1y, s1z);
     const double k1 = ta * inv_m0;
     const double q2x = q0x + k1 * s1x, q2y = q0y + k1 * s1y, q2z = q0z + k1 * s1z;
-    group_momentum<G>(m, vkx, vky, vkz, s3x, s3y, s3z);
-    jump_vjp<G>(a, m, vkx, vky, vkz, tc * inv_m0, m0, s3x, s3y, s3z, leader);
+    jump_vjp<G>(a, m, vkx, vky, vkz, tc * inv_m0, inv_m0);
     double gmu = 0.0;
     interaction_vjp<G>(ex, q2x, q2y, q2z, m, ti, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, a.m);
-    gr_vjp(q2x, q2y, q2z, kg, m0, ti, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, gmu);
+    gr_vjp(q2x, q2y, q2z, kg, inv_m0, ti, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, gmu);
     a.m0 += gmu;
-    jump_vjp<G>(a, m, v0x, v0y, v0z, k1, m0, s1x, s1y, s1z, leader);
+    jump_vjp<G>(a, m, v0x, v0y, v0z, k1, inv_m0);
   } else {
-    double s2x, s2y, s2z;
-    group_momentum<G>(m, vkx, vky, vkz, s2x, s2y, s2z);
-    jump_vjp<G>(a, m, vkx, vky, vkz, (ta + tc) * inv_m0, m0, s2x, s2y, s2z, leader);
+    jump_vjp<G>(a, m, vkx, vky, vkz, (ta + tc) * inv_m0, inv_m0);
     interaction_vjp<G>(ex, q0x, q0y, q0z, m, ti, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, a.m);
   }
 }
@@ -1411,9 +1415,6 @@ __device__ void adj_sweep_lane(const AdjParams& q, int slot, int lane) {
   const double kg = GR ? p.kgr * m0 * m0 : 0.0;
   Grad a;
   load_grad(q.grad, ns, slot, a);
-  // the lane(s) of planet 0 add the star-mass terms of the jump (in the
-  // split layout both copies, so that the copies keep equal bits)
-  const bool leader = G == G_SPLIT ? (lane & 14) == 0 : (lane & (G - 1)) == 0;
   if constexpr (SCH == SCHEME_SABA) {
     const int nu = p.saba_n;
     const double c1dt = p.sc[0] * dt;
@@ -1433,8 +1434,8 @@ __device__ void adj_sweep_lane(const AdjParams& q, int slot, int lane) {
       kepler_at_X(q0x, q0y, q0z, v0x, v0y, v0z, m0, tau, cur.v[6], kf);
       const double q1x = kf.f * q0x + kf.g * v0x, q1y = kf.f * q0y + kf.g * v0y, q1z = kf.f * q0z + kf.g * v0z;
       const double v1x = kf.fd * q0x + kf.gd * v0x, v1y = kf.fd * q0y + kf.gd * v0y, v1z = kf.fd * q0z + kf.gd * v0z;
-      kick_block_vjp<G, false>(a, ex, m, m0, inv_m0, 0.0, q1x, q1y, q1z, v1x, v1y, v1z, vkx, vky, vkz, 0.5 * tb, tb,
-                               0.5 * tb, leader);
+      kick_block_vjp<G, false>(a, ex, m, inv_m0, 0.0, q1x, q1y, q1z, v1x, v1y, v1z, vkx, vky, vkz, 0.5 * tb, tb,
+                               0.5 * tb);
       double gmu = 0.0;
       kepler_vjp(kf, q0x, q0y, q0z, v0x, v0y, v0z, m0, a.qx, a.qy, a.qz, a.vx, a.vy, a.vz, gmu);
       a.m0 += gmu;
@@ -1474,8 +1475,7 @@ __device__ void adj_sweep_lane(const AdjParams& q, int slot, int lane) {
       double gmu = 0.0;
       kepler_vjp(k, q3x, q3y, q3z, vkx, vky, vkz, m0, a.qx, a.qy, a.qz, a.vx, a.vy, a.vz, gmu);
       a.m0 += gmu;
-      kick_block_vjp<G, GR>(a, ex, m, m0, inv_m0, kg, q0x, q0y, q0z, v0x, v0y, v0z, vkx, vky, vkz, ta, ti, h,
-                            leader);
+      kick_block_vjp<G, GR>(a, ex, m, inv_m0, kg, q0x, q0y, q0z, v0x, v0y, v0z, vkx, vky, vkz, ta, ti, h);
     }
     store_grad(q.grad, ns, slot, a);
     return;
@@ -1502,20 +1502,14 @@ __device__ void adj_sweep_lane(const AdjParams& q, int slot, int lane) {
       group_momentum<G>(m, v1x, v1y, v1z, s1x, s1y, s1z);
       double kj = h * inv_m0;
       double q2x = q1x + kj * s1x, q2y = q1y + kj * s1y, q2z = q1z + kj * s1z;
-      double v3x = vkx, v3y = vky, v3z = vkz;   // V after the kick, from the tape
-      double s3x, s3y, s3z;
-      group_momentum<G>(m, v3x, v3y, v3z, s3x, s3y, s3z);
-      jump_vjp<G>(a, m, v3x, v3y, v3z, kj, m0, s3x, s3y, s3z, leader);
+      jump_vjp<G>(a, m, vkx, vky, vkz, kj, inv_m0);
       double gmu = 0.0;
       interaction_vjp<G>(ex, q2x, q2y, q2z, m, dt, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, a.m);
-      gr_vjp(q2x, q2y, q2z, kg, m0, dt, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, gmu);
+      gr_vjp(q2x, q2y, q2z, kg, inv_m0, dt, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, gmu);
       a.m0 += gmu;
-      jump_vjp<G>(a, m, v1x, v1y, v1z, kj, m0, s1x, s1y, s1z, leader);
+      jump_vjp<G>(a, m, v1x, v1y, v1z, kj, inv_m0);
     } else {
-      double v2x = vkx, v2y = vky, v2z = vkz;   // V after the kick, from the tape
-      double s2x, s2y, s2z;
-      group_momentum<G>(m, v2x, v2y, v2z, s2x, s2y, s2z);
-      jump_vjp<G>(a, m, v2x, v2y, v2z, dt * inv_m0, m0, s2x, s2y, s2z, leader);
+      jump_vjp<G>(a, m, vkx, vky, vkz, dt * inv_m0, inv_m0);
       interaction_vjp<G>(ex, q1x, q1y, q1z, m, dt, a.vx, a.vy, a.vz, a.qx, a.qy, a.qz, a.m);
     }
     double gmu = 0.0;
@@ -1529,32 +1523,29 @@ __device__ void adj_sweep_lane(const AdjParams& q, int slot, int lane) {
 // slots of the lane).
 template <int G, bool GR>
 __device__ __forceinline__ void kick_block_vjp_pair(Grad& a, Grad& b, const PairMass& pm, double ma, double mb,
-                                                    double m0, double inv_m0, double kg, const double q0a[3],
+                                                    double inv_m0, double kg, const double q0a[3],
                                                     const double v0a[3], const double q0b[3], const double v0b[3],
                                                     const double vka[3], const double vkb[3], double ta, double ti,
-                                                    double tc, bool leader) {
+                                                    double tc) {
   double gqa[3], gqb[3];
   if (GR) {
-    double s1[3], s3[3], q2a[3], q2b[3];
+    double s1[3], q2a[3], q2b[3];
     pair_momentum<G>(ma, v0a[0], v0a[1], v0a[2], mb, v0b[0], v0b[1], v0b[2], s1[0], s1[1], s1[2]);
     const double k1 = ta * inv_m0;
     for (int k = 0; k < 3; ++k) { q2a[k] = q0a[k] + k1 * s1[k]; q2b[k] = q0b[k] + k1 * s1[k]; }
-    pair_momentum<G>(ma, vka[0], vka[1], vka[2], mb, vkb[0], vkb[1], vkb[2], s3[0], s3[1], s3[2]);
-    jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, tc * inv_m0, m0, s3, leader);
+    jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, tc * inv_m0, inv_m0);
     const double gva[3] = {a.vx, a.vy, a.vz}, gvb[3] = {b.vx, b.vy, b.vz};
     gqa[0] = a.qx; gqa[1] = a.qy; gqa[2] = a.qz; gqb[0] = b.qx; gqb[1] = b.qy; gqb[2] = b.qz;
     interaction_vjp_pair<G>(pm, ma, mb, q2a, q2b, gva, gvb, ti, gqa, gqb, a.m, b.m);
     double gmu_a = 0.0, gmu_b = 0.0;
-    gr_vjp(q2a[0], q2a[1], q2a[2], kg, m0, ti, gva[0], gva[1], gva[2], gqa[0], gqa[1], gqa[2], gmu_a);
-    gr_vjp(q2b[0], q2b[1], q2b[2], kg, m0, ti, gvb[0], gvb[1], gvb[2], gqb[0], gqb[1], gqb[2], gmu_b);
+    gr_vjp(q2a[0], q2a[1], q2a[2], kg, inv_m0, ti, gva[0], gva[1], gva[2], gqa[0], gqa[1], gqa[2], gmu_a);
+    gr_vjp(q2b[0], q2b[1], q2b[2], kg, inv_m0, ti, gvb[0], gvb[1], gvb[2], gqb[0], gqb[1], gqb[2], gmu_b);
     a.qx = gqa[0]; a.qy = gqa[1]; a.qz = gqa[2]; b.qx = gqb[0]; b.qy = gqb[1]; b.qz = gqb[2];
     a.m0 += gmu_a;
     b.m0 += gmu_b;
-    jump_vjp_pair<G>(a, b, ma, mb, v0a, v0b, k1, m0, s1, leader);
+    jump_vjp_pair<G>(a, b, ma, mb, v0a, v0b, k1, inv_m0);
   } else {
-    double s2[3];
-    pair_momentum<G>(ma, vka[0], vka[1], vka[2], mb, vkb[0], vkb[1], vkb[2], s2[0], s2[1], s2[2]);
-    jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, (ta + tc) * inv_m0, m0, s2, leader);
+    jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, (ta + tc) * inv_m0, inv_m0);
     const double gva[3] = {a.vx, a.vy, a.vz}, gvb[3] = {b.vx, b.vy, b.vz};
     gqa[0] = a.qx; gqa[1] = a.qy; gqa[2] = a.qz; gqb[0] = b.qx; gqb[1] = b.qy; gqb[2] = b.qz;
     interaction_vjp_pair<G>(pm, ma, mb, q0a, q0b, gva, gvb, ti, gqa, gqb, a.m, b.m);
@@ -1645,7 +1636,6 @@ __device__ void adj_sweep_pair(const AdjParams& q, int sa, int lane) {
   Grad a, b;
   load_grad(q.grad, ns, sa, a);
   load_grad(q.grad, ns, sb, b);
-  const bool leader = (lane & (G - 1)) == 0;
   if constexpr (SCH == SCHEME_SABA) {
     const int nu = p.saba_n;
     const double c1dt = p.sc[0] * dt;
@@ -1669,8 +1659,8 @@ __device__ void adj_sweep_pair(const AdjParams& q, int sa, int lane) {
         q1a[c] = ka.f * q0a[c] + ka.g * v0a[c]; v1a[c] = ka.fd * q0a[c] + ka.gd * v0a[c];
         q1b[c] = kb.f * q0b[c] + kb.g * v0b[c]; v1b[c] = kb.fd * q0b[c] + kb.gd * v0b[c];
       }
-      kick_block_vjp_pair<G, false>(a, b, pm, ma, mb, m0, inv_m0, 0.0, q1a, v1a, q1b, v1b, vka, vkb, 0.5 * tb, tb,
-                                    0.5 * tb, leader);
+      kick_block_vjp_pair<G, false>(a, b, pm, ma, mb, inv_m0, 0.0, q1a, v1a, q1b, v1b, vka, vkb, 0.5 * tb, tb,
+                                    0.5 * tb);
       double gmu = 0.0;
       kepler_vjp(ka, q0a[0], q0a[1], q0a[2], v0a[0], v0a[1], v0a[2], m0, a.qx, a.qy, a.qz, a.vx, a.vy, a.vz, gmu);
       a.m0 += gmu;
@@ -1716,8 +1706,7 @@ __device__ void adj_sweep_pair(const AdjParams& q, int sa, int lane) {
       gmu = 0.0;
       kepler_vjp(kb, q3b[0], q3b[1], q3b[2], vkb[0], vkb[1], vkb[2], m0, b.qx, b.qy, b.qz, b.vx, b.vy, b.vz, gmu);
       b.m0 += gmu;
-      kick_block_vjp_pair<G, GR>(a, b, pm, ma, mb, m0, inv_m0, kg, q0a, v0a, q0b, v0b, vka, vkb, ta, ti, h,
-                                 leader);
+      kick_block_vjp_pair<G, GR>(a, b, pm, ma, mb, inv_m0, kg, q0a, v0a, q0b, v0b, vka, vkb, ta, ti, h);
     }
     store_grad(q.grad, ns, sa, a);
     store_grad(q.grad, ns, sb, b);
@@ -1742,27 +1731,24 @@ __device__ void adj_sweep_pair(const AdjParams& q, int sa, int lane) {
     }
     double gqa[3] = {a.qx, a.qy, a.qz}, gqb[3] = {b.qx, b.qy, b.qz};
     if (GR) {
-      double s1[3], s3[3];
+      double s1[3];
       pair_momentum<G>(ma, v1a[0], v1a[1], v1a[2], mb, v1b[0], v1b[1], v1b[2], s1[0], s1[1], s1[2]);
       const double kj = h * inv_m0;
       double q2a[3], q2b[3];
       for (int k = 0; k < 3; ++k) { q2a[k] = q1a[k] + kj * s1[k]; q2b[k] = q1b[k] + kj * s1[k]; }
-      pair_momentum<G>(ma, vka[0], vka[1], vka[2], mb, vkb[0], vkb[1], vkb[2], s3[0], s3[1], s3[2]);
-      jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, kj, m0, s3, leader);
+      jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, kj, inv_m0);
       const double gva[3] = {a.vx, a.vy, a.vz}, gvb[3] = {b.vx, b.vy, b.vz};
       gqa[0] = a.qx; gqa[1] = a.qy; gqa[2] = a.qz; gqb[0] = b.qx; gqb[1] = b.qy; gqb[2] = b.qz;
       interaction_vjp_pair<G>(pm, ma, mb, q2a, q2b, gva, gvb, dt, gqa, gqb, a.m, b.m);
       double gmu_a = 0.0, gmu_b = 0.0;
-      gr_vjp(q2a[0], q2a[1], q2a[2], kg, m0, dt, gva[0], gva[1], gva[2], gqa[0], gqa[1], gqa[2], gmu_a);
-      gr_vjp(q2b[0], q2b[1], q2b[2], kg, m0, dt, gvb[0], gvb[1], gvb[2], gqb[0], gqb[1], gqb[2], gmu_b);
+      gr_vjp(q2a[0], q2a[1], q2a[2], kg, inv_m0, dt, gva[0], gva[1], gva[2], gqa[0], gqa[1], gqa[2], gmu_a);
+      gr_vjp(q2b[0], q2b[1], q2b[2], kg, inv_m0, dt, gvb[0], gvb[1], gvb[2], gqb[0], gqb[1], gqb[2], gmu_b);
       a.qx = gqa[0]; a.qy = gqa[1]; a.qz = gqa[2]; b.qx = gqb[0]; b.qy = gqb[1]; b.qz = gqb[2];
       a.m0 += gmu_a;
       b.m0 += gmu_b;
-      jump_vjp_pair<G>(a, b, ma, mb, v1a, v1b, kj, m0, s1, leader);
+      jump_vjp_pair<G>(a, b, ma, mb, v1a, v1b, kj, inv_m0);
     } else {
-      double s2[3];
-      pair_momentum<G>(ma, vka[0], vka[1], vka[2], mb, vkb[0], vkb[1], vkb[2], s2[0], s2[1], s2[2]);
-      jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, dt * inv_m0, m0, s2, leader);
+      jump_vjp_pair<G>(a, b, ma, mb, vka, vkb, dt * inv_m0, inv_m0);
       const double gva[3] = {a.vx, a.vy, a.vz}, gvb[3] = {b.vx, b.vy, b.vz};
       gqa[0] = a.qx; gqa[1] = a.qy; gqa[2] = a.qz; gqb[0] = b.qx; gqb[1] = b.qy; gqb[2] = b.qz;
       interaction_vjp_pair<G>(pm, ma, mb, q1a, q1b, gva, gvb, dt, gqa, gqb, a.m, b.m);
@@ -1977,8 +1963,8 @@ struct JacAdj {
 
 __device__ __forceinline__ void jac_mass_adj(const JacConst& jc, double m0, const JacAdj& g, Grad& a,
                                              double& gMim1) {
-  const double gMi = g.Mi - jc.w * g.w / jc.Mi;
-  a.m += g.w / jc.Mi + gMi;
+  const double gMi = g.Mi - jc.w * g.w * jc.inv_Mi;
+  a.m += g.w * jc.inv_Mi + gMi;
   a.m0 += jc.inv_Mim1 * g.ratio;
   const double ginv = g.inv + m0 * g.ratio;
   gMim1 += gMi - jc.inv_Mim1 * jc.inv_Mim1 * ginv;
@@ -2041,7 +2027,7 @@ __device__ __forceinline__ void kick_jacobi_vjp(Grad& a, double& gMim1, const Ex
                  vz = group_scan_incl<G>(jc.inv_Mim1 * Gz, p);
     a.m += vx * grx + vy * gry + vz * grz;
     double gmu = 0.0;
-    gr_vjp(qx, qy, qz, kg, m0, 1.0, Gx + m * vx, Gy + m * vy, Gz + m * vz, gqx, gqy, gqz, gmu);
+    gr_vjp(qx, qy, qz, kg, jc.inv_m0, 1.0, Gx + m * vx, Gy + m * vy, Gz + m * vz, gqx, gqy, gqz, gmu);
     a.m0 += gmu;
   }
   // wq = m |q|^-3, kq = M_i ratio |q|^-3, kp = M_i |x'|^-3
@@ -2480,9 +2466,7 @@ template <int G, bool GR> __device__ void adj_init_kdk_lane(const AdjParams& q, 
     const double q0x = L.qx, q0y = L.qy, q0z = L.qz, v0x = L.vx, v0y = L.vy, v0z = L.vz;
     double vkx, vky, vkz;
     kick_block<G, GR, 1>(L, ex, inv_m0, kg, h, h, 0.0, vkx, vky, vkz);
-    const bool leader = G == G_SPLIT ? (lane & 14) == 0 : (lane & (G - 1)) == 0;
-    kick_block_vjp<G, GR>(a, ex, L.m, m0, inv_m0, kg, q0x, q0y, q0z, v0x, v0y, v0z, vkx, vky, vkz, h, h, 0.0,
-                          leader);
+    kick_block_vjp<G, GR>(a, ex, L.m, inv_m0, kg, q0x, q0y, q0z, v0x, v0y, v0z, vkx, vky, vkz, h, h, 0.0);
   }
   store_grad(q.grad, ns, slot, a);
 }
@@ -2503,8 +2487,7 @@ template <int G, bool GR> __device__ void adj_init_kdk_pair(const AdjParams& q, 
     const double q0b[3] = {B.qx, B.qy, B.qz}, v0b[3] = {B.vx, B.vy, B.vz};
     double vka[3], vkb[3];
     kick_block_pair<G, GR>(A, B, pm, inv_m0, kg, h, h, 0.0, vka, vkb);
-    kick_block_vjp_pair<G, GR>(a, b, pm, A.m, B.m, m0, inv_m0, kg, q0a, v0a, q0b, v0b, vka, vkb, h, h, 0.0,
-                               (lane & (G - 1)) == 0);
+    kick_block_vjp_pair<G, GR>(a, b, pm, A.m, B.m, inv_m0, kg, q0a, v0a, q0b, v0b, vka, vkb, h, h, 0.0);
   }
   store_grad(q.grad, ns, sa, a);
   store_grad(q.grad, ns, sb, b);

@@ -10,48 +10,42 @@
 
 namespace wh {
 
-// Stumpff functions c2..c5 by series (K terms of c4 and c5, then the
-// recurrence c_n = 1/n! - z c_{n+2}), for the G functions G0..G5 the Kepler
-// derivatives need.
-template <int K> __device__ __forceinline__ void stumpff_c0_c5(double z, double c[6]) {
-  c[4] = stumpff_series<K, 4>(z);
-  c[5] = stumpff_series<K, 5>(z);
-  c[2] = fma(-z, c[4], 0.5);
-  c[3] = fma(-z, c[5], 1.0 / 6.0);
-  c[0] = fma(-z, c[2], 1.0);
-  c[1] = fma(-z, c[3], 1.0);
-}
-
 // Forward quantities of one Kepler drift at a known anomaly X.
 struct KepFwd {
-  double r0, eta, beta, zeta, X;
+  double r0, ir0, eta, beta, zeta, X;
   double G[6];
-  double r, f, g, fd, gd;
+  double ir, f, g, fd, gd;
 };
 
+// G4 and G5 by series, the lower ones by G_n = X^n/n! - beta G_{n+2}.  The
+// reciprocals 1/r0 and 1/r are the refined hardware seeds of the forward
+// solve: with the IEEE square root and divisions in their place (1/r0, 1/r
+// and the quotients by mu, r0 r and r) a sweep step issued a fifth more
+// instructions, and the sweep is bound by their issue.
 __device__ __forceinline__ void kepler_at_X(double qx, double qy, double qz, double vx, double vy, double vz,
                                             double mu, double tau, double X, KepFwd& k) {
-  double r2 = fma(qx, qx, fma(qy, qy, qz * qz));
-  double v2 = fma(vx, vx, fma(vy, vy, vz * vz));
+  const double r2 = fma(qx, qx, fma(qy, qy, qz * qz));
+  const double v2 = fma(vx, vx, fma(vy, vy, vz * vz));
   k.eta = fma(qx, vx, fma(qy, vy, qz * vz));
-  k.r0 = sqrt(r2);
-  k.beta = 2.0 * mu / k.r0 - v2;
+  k.ir0 = rsqrt_full(r2);
+  k.r0 = r2 * k.ir0;
+  const double mi = mu * k.ir0;
+  k.beta = fma(2.0, mi, -v2);
   k.zeta = fma(-k.beta, k.r0, mu);
   k.X = X;
-  double X2 = X * X;
-  double c[6];
-  stumpff_c0_c5<8>(k.beta * X2, c);
-  double Xn = 1.0;
-#pragma unroll
-  for (int n = 0; n < 6; ++n) {
-    k.G[n] = Xn * c[n];
-    Xn *= X;
-  }
-  k.r = fma(k.eta, k.G[1], fma(k.zeta, k.G[2], k.r0));
-  k.f = 1.0 - mu * k.G[2] / k.r0;
+  const double X2 = X * X, X3 = X2 * X, z = k.beta * X2;
+  k.G[4] = X2 * X2 * stumpff_series<8, 4>(z);
+  k.G[5] = X2 * X3 * stumpff_series<8, 5>(z);
+  k.G[2] = fma(-k.beta, k.G[4], 0.5 * X2);
+  k.G[3] = fma(-k.beta, k.G[5], (1.0 / 6.0) * X3);
+  k.G[1] = fma(-k.beta, k.G[3], X);
+  k.G[0] = fma(-k.beta, k.G[2], 1.0);
+  const double r = fma(k.eta, k.G[1], fma(k.zeta, k.G[2], k.r0));
+  k.ir = rcp_full(r);
+  k.f = fma(-mi, k.G[2], 1.0);
   k.g = fma(-mu, k.G[3], tau);
-  k.fd = -mu * k.G[1] / (k.r0 * k.r);
-  k.gd = 1.0 - mu * k.G[2] / k.r;
+  k.fd = -(mi * k.ir) * k.G[1];
+  k.gd = fma(-(mu * k.ir), k.G[2], 1.0);
 }
 
 // Adjoint of the Kepler drift.  In: (gQ1, gV1), the adjoint of the output.
@@ -73,13 +67,15 @@ __device__ __forceinline__ void kepler_vjp(const KepFwd& k, double qx, double qy
   double nqx = k.f * gqx + k.fd * gvx, nqy = k.f * gqy + k.fd * gvy, nqz = k.f * gqz + k.fd * gvz;
   double nvx = k.g * gqx + k.gd * gvx, nvy = k.g * gqy + k.gd * gvy, nvz = k.g * gqz + k.gd * gvz;
   // f = 1 - mu G2/r0, g = tau - mu G3, f' = -mu G1/(r0 r), g' = 1 - mu G2/r
-  double ir0 = 1.0 / k.r0, ir = 1.0 / k.r;
-  double gm = -gf * G[2] * ir0 - gg * G[3] + gfd * k.fd / mu - ggd * G[2] * ir;
-  double gG1 = -gfd * mu * ir0 * ir;
-  double gG2 = -gf * mu * ir0 - ggd * mu * ir;
+  const double ir0 = k.ir0, ir = k.ir;
+  const double a0 = gf * ir0, a1 = ggd * ir, b = gfd * (ir0 * ir);
+  double gm = -(a0 * G[2] + gg * G[3] + b * G[1] + a1 * G[2]);
+  double gG1 = -mu * b;
+  double gG2 = -mu * (a0 + a1);
   double gG3 = -gg * mu;
-  double gr0 = gf * mu * G[2] * ir0 * ir0 - gfd * k.fd * ir0;
-  double gr = -gfd * k.fd * ir + ggd * mu * G[2] * ir * ir;
+  const double w = mu * b * G[1];          // -gfd f'
+  double gr0 = ir0 * fma(mu * a0, G[2], w);
+  double gr = ir * fma(mu * a1, G[2], w);
   // r = r0 + eta G1 + zeta G2
   gr0 += gr;
   double geta = gr * G[1];
@@ -105,16 +101,17 @@ __device__ __forceinline__ void kepler_vjp(const KepFwd& k, double qx, double qy
   gbeta -= gzeta * k.r0;
   gr0 -= gzeta * k.beta;
   // beta = 2 mu / r0 - |V|^2
-  gm += 2.0 * gbeta * ir0;
-  gr0 -= 2.0 * gbeta * mu * ir0 * ir0;
-  double gv2 = -gbeta;
+  const double gb = 2.0 * gbeta * ir0;
+  gm += gb;
+  gr0 -= gb * mu * ir0;
   // eta = Q.V, |V|^2, r0 = |Q|
-  nqx += geta * vx + gr0 * qx * ir0;
-  nqy += geta * vy + gr0 * qy * ir0;
-  nqz += geta * vz + gr0 * qz * ir0;
-  nvx += geta * qx + 2.0 * gv2 * vx;
-  nvy += geta * qy + 2.0 * gv2 * vy;
-  nvz += geta * qz + 2.0 * gv2 * vz;
+  const double gq = gr0 * ir0, gv = -2.0 * gbeta;
+  nqx += geta * vx + gq * qx;
+  nqy += geta * vy + gq * qy;
+  nqz += geta * vz + gq * qz;
+  nvx += geta * qx + gv * vx;
+  nvy += geta * qy + gv * vy;
+  nvz += geta * qz + gv * vz;
   gqx = nqx; gqy = nqy; gqz = nqz;
   gvx = nvx; gvy = nvy; gvz = nvz;
   gmu += gm;
@@ -187,12 +184,13 @@ __device__ __forceinline__ void interaction_vjp_dpp(const DppMass& t, double qx,
 }
 
 // Adjoint of the GR kick V += tau * (-kg Q/|Q|^4), kg = 6 mu^2 / c^2:
-//   gQ += -tau kg (gV/|Q|^4 - 4 Q (Q.gV)/|Q|^6),  gmu += tau gV.a_GR * 2/mu.
-__device__ __forceinline__ void gr_vjp(double qx, double qy, double qz, double kg, double mu, double tau,
+//   gQ += -tau kg (gV/|Q|^4 - 4 Q (Q.gV)/|Q|^6),  gmu += tau gV.a_GR * 2/mu,
+// inv_mu = 1/mu.
+__device__ __forceinline__ void gr_vjp(double qx, double qy, double qz, double kg, double inv_mu, double tau,
                                        double gvx, double gvy, double gvz, double& gqx, double& gqy, double& gqz,
                                        double& gmu) {
   double r2 = qx * qx + qy * qy + qz * qz;
-  double ir2 = 1.0 / r2;
+  double ir2 = rcp_full(r2);
   double ir4 = ir2 * ir2;
   double qg = qx * gvx + qy * gvy + qz * gvz;
   double s = -tau * kg * ir4;
@@ -200,7 +198,7 @@ __device__ __forceinline__ void gr_vjp(double qx, double qy, double qz, double k
   gqx += s * (gvx + w * qx);
   gqy += s * (gvy + w * qy);
   gqz += s * (gvz + w * qz);
-  gmu += 2.0 * s * qg / mu;
+  gmu += 2.0 * s * qg * inv_mu;
 }
 
 }  // namespace wh
