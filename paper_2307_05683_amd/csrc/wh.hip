@@ -2657,7 +2657,6 @@ struct EnvParams {
   double* zmax_out;  // [n] or null
   int64_t n;
   int64_t n_steps;
-  KepCountsRun counts;
 };
 
 __device__ __forceinline__ double semi_major(double qx, double qy, double qz, double vx, double vy, double vz,
@@ -2667,8 +2666,14 @@ __device__ __forceinline__ double semi_major(double qx, double qy, double qz, do
   return 1.0 / (2.0 / r - v2 / mu);
 }
 
-__global__ __launch_bounds__(256) void k_envelope(EnvParams p) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < p.n; i += (int64_t)gridDim.x * 256) {
+// A drift is one serial chain per particle, so a wavefront's time is its
+// latency and issue.  With the series lengths compiled in (KepCountsTerms) a
+// series is a run of FMAs on constants; with lengths at run time every term
+// waited for its own load of a constant from memory.
+// One-wave workgroups: 32768 particles are 512 wavefronts, which then take a
+// SIMD each on all 256 compute units instead of four on each of 128.
+template <class P> __global__ __launch_bounds__(64) void k_envelope(EnvParams p, P counts) {
+  for (int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x; i < p.n; i += (int64_t)gridDim.x * 64) {
     double qx = p.Q[3 * i], qy = p.Q[3 * i + 1], qz = p.Q[3 * i + 2];
     double vx = p.V[3 * i], vy = p.V[3 * i + 1], vz = p.V[3 * i + 2];
     const double mu = p.mu[i], tau = p.tau[i];
@@ -2676,7 +2681,7 @@ __global__ __launch_bounds__(256) void k_envelope(EnvParams p) {
     KepDiag dg{0.0, 1e300};
     for (int64_t s = 0; s < p.n_steps; ++s) {
       KepCoef k;
-      kepler_coeffs_p(p.counts, qx, qy, qz, vx, vy, vz, mu, tau, dg, k);
+      kepler_coeffs_p(counts, qx, qy, qz, vx, vy, vz, mu, tau, dg, k);
       double nqx = qx + fma(k.fm1, qx, k.g * vx);
       double nqy = qy + fma(k.fm1, qy, k.g * vy);
       double nqz = qz + fma(k.fm1, qz, k.g * vz);
@@ -2700,6 +2705,32 @@ __global__ __launch_bounds__(256) void k_envelope(EnvParams p) {
 // Host side
 // ===========================================================================
 namespace {
+
+// Series lengths compiled into the explorer's kernel: the default search
+// space of the Python layer (2..6 terms in the Halley steps, 4..9 in the
+// Newton steps), the integrator's sets among it; other lengths run the
+// kernel that takes them at run time, with the same operations in the same
+// order.
+constexpr int ENV_KH0 = 2, ENV_KH1 = 6, ENV_KN0 = 4, ENV_KN1 = 9;
+
+void launch_envelope_rt(const EnvParams& p, int blocks, int h, int n, int kh, int kn, hipStream_t st) {
+  hipLaunchKernelGGL((k_envelope<KepCountsRun>), dim3(blocks), dim3(64), 0, st, p, KepCountsRun{h, n, kh, kn});
+}
+template <int KH, int KN>
+void launch_envelope(const EnvParams& p, int blocks, int h, int n, int kh, int kn, hipStream_t st) {
+  if constexpr (KH > ENV_KH1) {
+    launch_envelope_rt(p, blocks, h, n, kh, kn, st);
+  } else if (kh != KH) {
+    launch_envelope<KH + 1, KN>(p, blocks, h, n, kh, kn, st);
+  } else if constexpr (KN > ENV_KN1) {
+    launch_envelope_rt(p, blocks, h, n, kh, kn, st);
+  } else if (kn != KN) {
+    launch_envelope<KH, KN + 1>(p, blocks, h, n, kh, kn, st);
+  } else {
+    hipLaunchKernelGGL((k_envelope<KepCountsTerms<KH, KN>>), dim3(blocks), dim3(64), 0, st, p,
+                       KepCountsTerms<KH, KN>{h, n});
+  }
+}
 
 thread_local std::string g_err;
 
@@ -3537,9 +3568,8 @@ wh_status wh_kepler_envelope(int64_t n, const double* Q, const double* V, const 
   p.Q = Q; p.V = V; p.mu = mu; p.tau = tau;
   p.Q_out = Q_out; p.V_out = V_out; p.a_err = a_err; p.zmax_out = zmax_out;
   p.n = n; p.n_steps = n_steps;
-  p.counts = KepCountsRun{n_halley, n_newton, terms_halley, terms_newton};
-  int64_t blocks = std::min<int64_t>((n + 255) / 256, 1 << 20);
-  hipLaunchKernelGGL(k_envelope, dim3((unsigned)blocks), dim3(256), 0, stream, p);
+  const int blocks = (int)std::min<int64_t>((n + 63) / 64, 1 << 20);
+  launch_envelope<ENV_KH0, ENV_KN0>(p, blocks, n_halley, n_newton, terms_halley, terms_newton, stream);
   return hip_check(hipGetLastError(), "envelope launch");
 }
 

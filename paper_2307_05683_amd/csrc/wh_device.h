@@ -270,6 +270,17 @@ template <int N0> __device__ __forceinline__ double stumpff_series_rt(double z, 
   return s;
 }
 
+// Iteration counts at run time, series lengths compiled in (the explorer's
+// usual lengths).
+template <int KH, int KN> struct KepCountsTerms {
+  static constexpr bool recur = false;
+  int h, n;
+  __device__ int nh() const { return h; }
+  __device__ int nn() const { return n; }
+  template <int N0> __device__ static double series_h(double z) { return stumpff_series<KH, N0>(z); }
+  template <int N0> __device__ static double series_n(double z) { return stumpff_series<KN, N0>(z); }
+};
+
 // Run-time counts; limits keep every table index in range.
 constexpr int KEP_RT_MAX_NH = 8, KEP_RT_MAX_NN = 8, KEP_RT_MAX_TERMS = 14;
 struct KepCountsRun {
