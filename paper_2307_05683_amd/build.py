@@ -8,6 +8,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = os.path.join(PKG, "csrc", "wh.hip")
 PAIR_SRC = os.path.join(PKG, "csrc", "wh_pair_step.hip")
+WIDE_SRC = os.path.join(PKG, "csrc", "wh_wide_step.hip")
 LIB = os.path.join(PKG, "libwh.so")
 ARCH = os.environ.get("WH_OFFLOAD_ARCH", "gfx950")
 
@@ -45,12 +46,12 @@ def _hipcc(cmd, out, verbose):
 
 
 def build(verbose: bool = False, extra=()) -> str:
-    # two translation units compiled side by side, then linked into one
+    # three translation units compiled side by side, then linked into one
     # shared library (each object carries its own gfx950 code object)
     cflags = [f for f in FLAGS if f != "-shared"] + list(extra)
     with tempfile.TemporaryDirectory() as tmp:
         jobs = []
-        for src, more in ((SRC, []), (PAIR_SRC, PAIR_FLAGS)):
+        for src, more in ((SRC, []), (PAIR_SRC, PAIR_FLAGS), (WIDE_SRC, [])):
             obj = os.path.join(tmp, os.path.basename(src) + ".o")
             # a fixed compilation-unit id: the default one hashes the
             # temporary object path, which would make every build differ

@@ -29,6 +29,7 @@
 #include "wh_pair.h"
 #include "wh_split.h"
 #include "wh_step.h"
+#include "wh_wide.h"
 #include "wh_host.h"
 
 using namespace wh;
@@ -1217,6 +1218,7 @@ struct AdjParams {
   int n_seg;           // steps of the segment being swept
   int first_synced;    // it starts from the synchronized initial state
   int sweep_waves;     // wavefronts of the sweeping role (0: the launch only records)
+  int wide_record;     // wavefronts of the recording role with four lanes per planet (0: a lane each)
   const double* ck_rec;  // recording role: checkpoint of the segment to record,
   double* tape_rec;      // the tape to fill,
   int n_rec;             // its steps,
@@ -1785,13 +1787,26 @@ template <bool GR, int SCH> __global__ __launch_bounds__(256) void k_adj_segment
 }
 
 // Waves [0, sweep_waves) sweep one segment, the waves after them record the
-// previous segment; each role covers the packing's waves once.
-template <bool GR, bool SPLIT, int SCH> __global__ __launch_bounds__(256) void k_adj_segment(AdjParams q) {
+// previous segment; each role covers the packing's waves once.  Contexts whose
+// step runs with four lanes per planet record in that form too (the same bits
+// as the step, which recording repeats).
+template <bool GR, bool SPLIT, int SCH> __global__ __launch_bounds__(64) void k_adj_segment(AdjParams q) {
+  __shared__ double lds[WIDE_LDS];
   const StepParams& p = q.sp;
-  const int lane = threadIdx.x & 63;
-  int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const int lane = threadIdx.x;
+  int wave = (int)blockIdx.x;
   const bool sweep = wave < q.sweep_waves;
   if (!sweep) wave -= q.sweep_waves;
+  if (!sweep && q.wide_record > 0) {
+    if (wave >= q.wide_record) return;
+    const bool first = q.rec_first_synced != 0;
+    if (SPLIT) wide_record<8, GR, SCH, 1>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else if (wave < 4 * p.w1) wide_record<1, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else if (wave < 4 * p.w2) wide_record<2, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else if (wave < 4 * p.w4) wide_record<4, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else wide_record<8, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    return;
+  }
   if (wave >= p.w8) return;
   const int slot = wave * 64 + lane;
   if (SPLIT) {
@@ -2669,7 +2684,9 @@ __device__ __forceinline__ double semi_major(double qx, double qy, double qz, do
 // A drift is one serial chain per particle, so a wavefront's time is its
 // latency and issue.  With the series lengths compiled in (KepCountsTerms) a
 // series is a run of FMAs on constants; with lengths at run time every term
-// waited for its own load of a constant from memory.
+// waited for its own load of a constant from memory.  32768 particles, 730
+// drifts at the counts 2, 2, 4, 8: 415 us, 1660 us before (with four-wave
+// workgroups).
 // One-wave workgroups: 32768 particles are 512 wavefronts, which then take a
 // SIMD each on all 256 compute units instead of four on each of 128.
 template <class P> __global__ __launch_bounds__(64) void k_envelope(EnvParams p, P counts) {
@@ -2778,6 +2795,8 @@ struct wh_ctx {
   int* plan_wave = nullptr;
   int* plan_steps = nullptr;
   int plan_slots = 0;   // wavefronts the GPU holds at the kernel's occupancy
+  int wide_waves = 0;   // wavefronts of the step with four lanes per planet (0: not used)
+  int wide_block = 1;   // and of its workgroups
 };
 
 namespace {
@@ -2898,9 +2917,55 @@ void launch_step_kernel(const wh_ctx* c, const StepParams& p, int n_waves, hipSt
   (void)hipLaunchKernel(step_kernel(c), grid, block, args, smem, st);
 }
 
+// The step with four lanes per planet (wh_wide.h).
+template <int STORAGE> const void* wide_kernel_of(const wh_ctx* c) {
+  const bool gr = c->cfg.gr_c > 0, dkd = c->cfg.scheme == WH_DKD;
+  if (c->cfg.scheme >= WH_SABA2) return (const void*)k_step_wide<false, SCHEME_SABA, 0, STORAGE>;
+  if (c->cfg.kepler_counts == 1) {
+    if (dkd) return gr ? (const void*)k_step_wide<true, WH_DKD, 1, STORAGE> : (const void*)k_step_wide<false, WH_DKD, 1, STORAGE>;
+    return gr ? (const void*)k_step_wide<true, WH_KDK, 1, STORAGE> : (const void*)k_step_wide<false, WH_KDK, 1, STORAGE>;
+  }
+  if (dkd) return gr ? (const void*)k_step_wide<true, WH_DKD, 0, STORAGE> : (const void*)k_step_wide<false, WH_DKD, 0, STORAGE>;
+  return gr ? (const void*)k_step_wide<true, WH_KDK, 0, STORAGE> : (const void*)k_step_wide<false, WH_KDK, 0, STORAGE>;
+}
+void launch_wide(const wh_ctx* c, const StepParams& p, hipStream_t st) {
+  StepParams q = p;
+  void* args[] = {(void*)&q};
+  const dim3 block(64 * c->wide_block), grid((c->wide_waves + c->wide_block - 1) / c->wide_block);
+  (void)hipLaunchKernel(c->P.split ? wide_kernel_of<1>(c) : wide_kernel_of<0>(c), grid, block, args, 0, st);
+}
+
+// Whether the step runs with four lanes per planet: in the one-planet and
+// split packings of a DHC context with the DPP exchange, while its
+// wavefronts (four times the one-planet packing's, twice the split packing's)
+// are no more than the GPU has SIMDs.  Eight-planet systems without GR, us per
+// step with and without it: one system 0.63 and 0.91 (split packing 0.62 and
+// 0.74), 2048 systems, a wavefront per SIMD, 0.71 and 0.92 (0.71 and 0.75); at
+// 3072, 1.5 per SIMD, it would take 1.12 against 0.92.  Four planets: 4096
+// systems 0.62 and 0.71, 8192 systems 1.06 and 0.72; two planets: 8192 systems
+// 0.54 and 0.62, 16384 systems 0.98 and 0.63.
+wh_status choose_wide(wh_ctx* c) {
+  c->wide_waves = 0;
+  if (c->cfg.coords != WH_COORDS_DHC || c->P.pair || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP)
+    return WH_OK;
+  int dev = 0, ncu = 0;
+  wh_status st;
+  if ((st = hip_check(hipGetDevice(&dev), "hipGetDevice")) ||
+      (st = hip_check(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev), "CU count")))
+    return st;
+  const int64_t waves = c->P.ns / (c->P.split ? 2 * WIDE_SLOTS : WIDE_SLOTS);
+  if (waves > (int64_t)4 * ncu) return WH_OK;   // four SIMDs per compute unit
+  c->wide_waves = (int)waves;
+  // one-wave workgroups go to compute units in turn; beyond one per unit,
+  // four-wave workgroups give each wavefront a SIMD of its own
+  c->wide_block = waves > ncu ? 4 : 1;
+  return WH_OK;
+}
+
 void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
   StepParams p = step_params(c, n_steps);
-  launch_step_kernel(c, p, c->P.nwaves, st);
+  if (c->wide_waves > 0) launch_wide(c, p, st);
+  else launch_step_kernel(c, p, c->P.nwaves, st);
 }
 
 // Balanced launch windows for one chunk (wh_config.balance): slots =
@@ -2914,7 +2979,7 @@ wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
   c->plan_slots = 0;
   hw.clear();
   hs.clear();
-  if (c->cfg.balance != 1 || c->P.serial) return WH_OK;
+  if (c->cfg.balance != 1 || c->P.serial || c->wide_waves > 0) return WH_OK;
   int dev = 0, ncu = 0, nb = 0;
   wh_status st;
   if ((st = hip_check(hipGetDevice(&dev), "hipGetDevice")) ||
@@ -3063,7 +3128,7 @@ void launch_adj_segment(const wh_ctx* c, const AdjParams& q, int sweep_waves, in
     hipLaunchKernelGGL((k_adj_segment_serial<GR, SCH>), grid, block, smem, st, q);
     return;
   }
-  const dim3 grid(sweep_waves + record_waves), block(64);
+  const dim3 grid(sweep_waves + (record_waves > 0 && c->wide_waves > 0 ? c->wide_waves : record_waves)), block(64);
   if (c->P.pair) hipLaunchKernelGGL((k_adj_segment_pair<GR, SCH>), grid, block, 0, st, q);
   else if (c->P.split) hipLaunchKernelGGL((k_adj_segment<GR, true, SCH>), grid, block, 0, st, q);
   else hipLaunchKernelGGL((k_adj_segment<GR, false, SCH>), grid, block, 0, st, q);
@@ -3189,7 +3254,7 @@ wh_status wh_init(wh_ctx** out, const wh_config* cfg, const int32_t* n_planets, 
     return s;
   };
   std::vector<int> plan_w, plan_s;   // outlive the copies: the stream is synchronized below
-  if ((st = build_plan(c, plan_w, plan_s))) return abandon(st);
+  if ((st = choose_wide(c)) || (st = build_plan(c, plan_w, plan_s))) return abandon(st);
   if (!plan_w.empty() &&
       ((st = hip_check(hipMemcpyAsync(c->plan_wave, plan_w.data(), sizeof(int) * plan_w.size(),
                                       hipMemcpyHostToDevice, stream), "upload launch plan")) ||
@@ -3458,6 +3523,7 @@ wh_status wh_adjoint_n(wh_ctx* c, void* tape, size_t tape_bytes, const double* g
   q.n_seg = 0;
   q.first_synced = 0;
   q.sweep_waves = 0;
+  q.wide_record = c->wide_waves;
   q.ck_rec = nullptr;
   q.tape_rec = seg[1];
   q.n_rec = 0;

@@ -1,0 +1,384 @@
+// Four lanes per planet: how small ensembles run the one-planet step.  256
+// VALU instructions per lane-step on eight-planet groups without GR (one lane
+// per planet: 457; the split layout: 382), 282 with GR (505; 440), and 15 LDS
+// instructions.
+//
+// An ensemble with few wavefronts leaves most SIMDs idle, and a step's time is
+// then the instructions one wavefront issues.  Here a wavefront runs 16 planet
+// slots instead of 64.  The four lanes of a planet repeat its Kepler solve (a
+// serial chain) and divide the rest: lane c < 3 carries component c of the
+// compensated state (lane 3 repeats lane 0), so the drift's map, the kicks'
+// increments, the momentum sum and the renormalization run once per lane
+// instead of three times, and every pair of a system is evaluated on a lane of
+// its own.  Each operation and each order of summation is that of the
+// one-planet step (wh_device.h, kick_block), so the results are the same bits
+// and the two mix freely (reverse mode's recording, the per-size path).
+//
+// Exchange goes through LDS, 2 KiB per wavefront.  A wavefront's own LDS
+// operations stay in order, so writing and reading need no wait between them,
+// only that the compiler keeps them apart (wave_lds_fence).  Per kick:
+//   1. every lane writes its component of the position and reads its own
+//      planet's and one partner's position whole, and its component of each
+//      partner's position;
+//   2. it evaluates 1/r^3 of its pair, writes it, and reads those of its
+//      planet's pairs;
+//   3. it adds the pairs' accelerations of its component, in the order of the
+//      rounds R1..R5 of interaction_accel_dpp.
+// Row h of 16 lanes holds four planets; an eight-planet group takes two rows.
+// Lane c of planet (h, r) evaluates the pair with
+//   c = 0: (h, r + 1)   R1            c = 1: (h, r + 2)   R2
+//   c = 2: (h', r + 1)  R3            c = 3: (h', r) R4 if h = 0, (h', r + 2) R5 if h = 1
+// (r modulo 4, h' the other row).  Positions and 1/r^3 are stored twice along
+// r, so that "r + k modulo 4" is a constant offset.
+#pragma once
+#include "wh_step.h"
+
+namespace wh {
+
+constexpr int WIDE_SLOTS = 16;   // planet slots per wavefront
+constexpr int WIDE_LDS = 256;    // doubles of LDS per wavefront
+
+constexpr int DPP_QUAD_0 = 0x00, DPP_QUAD_1 = 0x55, DPP_QUAD_2 = 0xAA;   // quad_perm: all lanes read lane 0, 1, 2
+constexpr int DPP_QUAD_REV = 0x1B;                                       // quad_perm [3,2,1,0]
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Values of the even and odd row of the lane's row pair, in every lane.
+__device__ __forceinline__ void row_pair(int v, int& even, int& odd) {
+  const auto s = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  even = (int)s[0];
+  odd = (int)s[1];
+}
+
+// group_sum over the planets of a group, of the lane's component: the same
+// butterfly, planet p ^ 1 four lanes away (half-row mirror, then each quad
+// reversed), p ^ 2 eight, and the other four planets in the other row.
+template <int G> __device__ __forceinline__ double wide_sum(double v) {
+#pragma clang fp contract(off)
+  if (G >= 2) v += dpp<DPP_QUAD_REV>(dpp<DPP_HALF_MIRROR>(v));
+  if (G >= 4) v += dpp<DPP_ROR8>(v);
+  if (G >= 8) {
+    int l0, l1, h0, h1;
+    row_pair(__double2loint(v), l0, l1);
+    row_pair(__double2hiint(v), h0, h1);
+    v = __hiloint2double(h0, l0) + __hiloint2double(h1, l1);
+  }
+  return v;
+}
+template <int G> __device__ __forceinline__ double wide_momentum(double m, double v) {
+#pragma clang fp contract(off)
+  return wide_sum<G>(m * v);
+}
+template <int G> __device__ __forceinline__ int wide_or(int f) {
+  if (G >= 2) f |= dpp_i<DPP_QUAD_REV>(dpp_i<DPP_HALF_MIRROR>(f));
+  if (G >= 4) f |= dpp_i<DPP_ROR8>(f);
+  if (G >= 8) {
+    int a, b;
+    row_pair(f, a, b);
+    f = a | b;
+  }
+  return f;
+}
+
+// Where a lane reads and writes the wavefront's LDS block (positions at
+// [row][8][4], 1/r^3 at 128 + [row][pair c][8]), and the partners' masses.
+template <int G> struct WideKick {
+  double* lds;
+  int iq, io, in, ip;            // own and other row's component, own planet, pair partner
+  int iw, ie, ier3, ie4, ie5;    // 1/r^3: the lane's own, its planet's
+  double m1, m1r, m2, m3, m3r, m4, m5;
+
+  __device__ __forceinline__ void init(double* block, int lane, double m) {
+    lds = block;
+    const int c = lane & 3, comp = c == 3 ? 0 : c, r = (lane >> 2) & 3, row = lane >> 4, odd = row & 1;
+    iq = row * 32 + r * 4 + comp;
+    in = row * 32 + r * 4;
+    io = (row ^ 1) * 32 + r * 4 + comp;
+    if (G == 8)
+      ip = c == 0 ? in + 4 : c == 1 ? in + 8 : (row ^ 1) * 32 + (r + (c == 2 ? 1 : 2 * odd)) * 4;
+    else if (G == 4)
+      ip = c == 1 ? in + 8 : in + 4;
+    else
+      ip = row * 32 + (r ^ 1) * 4;
+    iw = 128 + row * 32 + c * 8 + r;
+    ie = 128 + row * 32 + r;
+    ier3 = 128 + (row ^ 1) * 32 + 16 + r + 3;
+    ie4 = 128 + (row & ~1) * 32 + 24 + r;
+    ie5 = 128 + (row | 1) * 32 + 24 + (odd ? r : r + 2);
+    m1 = m1r = m2 = m3 = m3r = m4 = m5 = 0.0;
+    if (G == 1) return;
+    lds[iq] = m;
+    lds[iq + 16] = m;
+    wave_lds_fence();
+    if (G == 2) {
+      m1 = lds[ip];
+    } else {
+      m1 = lds[iq + 4]; m2 = lds[iq + 8]; m1r = lds[iq + 12];
+      if (G == 8) { m4 = lds[io]; m3 = lds[io + 4]; m5 = lds[io + 8]; m3r = lds[io + 12]; }
+    }
+    wave_lds_fence();
+  }
+
+  // Acceleration of the lane's component; q: the component of the position,
+  // (x, y, z): receives the planet's position.
+  __device__ __forceinline__ double accel(double q, double& x, double& y, double& z) const {
+#pragma clang fp contract(off)
+    lds[iq] = q;
+    if (G >= 4) lds[iq + 16] = q;
+    wave_lds_fence();
+    x = lds[in]; y = lds[in + 1]; z = lds[in + 2];
+    if (G == 1) return 0.0;
+    const double px = lds[ip], py = lds[ip + 1], pz = lds[ip + 2];
+    if (G == 2) {
+      const double q1 = lds[ip + (iq - in)];
+      const double dx = x - px, dy = y - py, dz = z - pz;
+      const double w = m1 * rsqrt3_full(fma(dx, dx, fma(dy, dy, dz * dz)));
+      return fma(-w, q - q1, 0.0);
+    }
+    const double q1 = lds[iq + 4], q2 = lds[iq + 8], q1r = lds[iq + 12];
+    double q4 = 0.0, q3 = 0.0, q5 = 0.0, q3r = 0.0;
+    if (G == 8) { q4 = lds[io]; q3 = lds[io + 4]; q5 = lds[io + 8]; q3r = lds[io + 12]; }
+    const double dx = x - px, dy = y - py, dz = z - pz;
+    const double ir3 = rsqrt3_full(fma(dx, dx, fma(dy, dy, dz * dz)));
+    lds[iw] = ir3;
+    lds[iw + 4] = ir3;
+    wave_lds_fence();
+    const double e1 = lds[ie], e1r = lds[ie + 3], e2 = lds[ie + 8];
+    double a = fma(-(m1 * e1), q - q1, 0.0);
+    a += (m1r * e1r) * (q1r - q);
+    a = fma(-(m2 * e2), q - q2, a);
+    if (G == 8) {
+      const double e3 = lds[ie + 16], e3r = lds[ier3], e4 = lds[ie4], e5 = lds[ie5];
+      a = fma(-(m3 * e3), q - q3, a);
+      a += (m3r * e3r) * (q3r - q);
+      a = fma(-(m4 * e4), q - q4, a);
+      a = fma(-(m5 * e5), q - q5, a);
+    }
+    return a;
+  }
+};
+
+// The lane's component of its planet's compensated state, and the planet's
+// constants.
+struct WideLane {
+  double q, v, cq, cv, m, m0, dt;
+  int sys, pl, first;
+};
+
+__device__ __forceinline__ int wide_comp(int lane) { return (lane & 3) == 3 ? 0 : lane & 3; }
+
+// Kepler drift (drift of wh_step.h): the whole planet's coefficients, the
+// lane's component of the map.  Returns the anomaly.
+template <int KC, class D>
+__device__ __forceinline__ double wide_drift(WideLane& L, double tau, D& dg) {
+  KepCoef k;
+  const double X = kepler_coeffs<KepSet<KC>::NH, KepSet<KC>::NN, KepSet<KC>::KH, KepSet<KC>::KN>(
+      dpp<DPP_QUAD_0>(L.q), dpp<DPP_QUAD_1>(L.q), dpp<DPP_QUAD_2>(L.q), dpp<DPP_QUAD_0>(L.v), dpp<DPP_QUAD_1>(L.v),
+      dpp<DPP_QUAD_2>(L.v), L.m0, tau, dg, k);
+  const double q0 = L.q, cq0 = L.cq;
+  linear_dd(k.fm1, L.q, L.cq, k.g, L.v, L.cv);
+  linear_dd(k.gdm1, L.v, L.cv, k.fd, q0, cq0);
+  return X;
+}
+
+// kick_block on the lane's component; vk: its velocity after the kick.
+template <int G, bool GR>
+__device__ __forceinline__ void wide_kick(WideLane& L, const WideKick<G>& wk, double inv_m0, double kg, double ta,
+                                          double ti, double tc, double& vk) {
+  double q = L.q, x, y, z;
+  if (GR) {
+    const double s = wide_momentum<G>(L.m, L.v), k1 = ta * inv_m0;
+    L.cq = fma(k1, s, L.cq);
+    q = fma(k1, s, q);
+  }
+  double a = wk.accel(q, x, y, z);
+  if (GR) a = fma(gr_weight(x, y, z, kg), q, a);
+  L.cv = fma(ti, a, L.cv);
+  vk = fma(ti, a, L.v);
+  const double s = wide_momentum<G>(L.m, vk);
+  L.cq = fma((GR ? tc : ta + tc) * inv_m0, s, L.cq);
+  renorm(L.q, L.cq);
+  renorm(L.v, L.cv);
+}
+
+// step_lane for four lanes per planet (DHC).
+template <int G, bool GR, int SCHEME, int KC>
+__device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, double* block, int lane) {
+  WideKick<G> wk;
+  wk.init(block, lane, L.m);
+  const double dt = L.dt, h = 0.5 * dt;
+  const double inv_m0 = 1.0 / L.m0;
+  const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
+  KepDiag dg{0.0, 1.0e300};
+  double vk;
+  const int n_steps = p.n_steps;
+  if constexpr (SCHEME == SCHEME_SABA) {
+    const double c1dt = p.sc[0] * dt;
+    const double sc1 = p.sc[1], sc2 = p.sc[2], sc3 = p.sc[3], sd0 = p.sd[0], sd1 = p.sd[1], sd2 = p.sd[2], sd3 = p.sd[3];
+    const int n_units = p.saba_n;
+    double tk = L.first ? c1dt : 2.0 * c1dt;
+    for (int s = 0; s < n_steps; ++s) {
+#pragma unroll 1
+      for (int k = 0; k < n_units; ++k) {
+        wide_drift<0>(L, tk, dg);
+        const double tb = (k == 0 ? sd0 : k == 1 ? sd1 : k == 2 ? sd2 : sd3) * dt;
+        wide_kick<G, false>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
+        tk = k + 1 < n_units ? (k == 0 ? sc1 : k == 1 ? sc2 : sc3) * dt : 2.0 * c1dt;
+      }
+    }
+  } else if (SCHEME == WH_DKD) {
+    double tk = L.first ? h : dt;
+    for (int s = 0; s < n_steps; ++s) {
+      wide_drift<KC>(L, tk, dg);
+      tk = dt;
+      wide_kick<G, GR>(L, wk, inv_m0, kg, h, dt, h, vk);
+    }
+  } else {
+    double ta = L.first ? 0.0 : h;
+    double ti = L.first ? h : dt;
+    for (int s = 0; s < n_steps; ++s) {
+      wide_kick<G, GR>(L, wk, inv_m0, kg, ta, ti, h, vk);
+      ta = h;
+      ti = dt;
+      wide_drift<KC>(L, dt, dg);
+    }
+  }
+  int f = 0;
+  if (L.pl >= 0) {
+    if (!__builtin_isfinite(L.q) || !__builtin_isfinite(L.v)) f |= WH_F_NONFINITE;
+    if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
+    if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
+  }
+  f |= dpp_i<DPP_QUAD_0>(f) | dpp_i<DPP_QUAD_1>(f) | dpp_i<DPP_QUAD_2>(f);   // the planet's three components
+  f = wide_or<G>(f);
+  if ((lane & (4 * G - 1)) == 0 && L.sys >= 0) {
+    p.flags[L.sys] |= (uint32_t)f;
+    p.synced[L.sys] = 0;
+  }
+}
+
+// Slot of a lane's planet.  STORAGE 0: one planet per lane (the groups of
+// the pow2 and G8 packings lie in planet order, so wavefront w takes slots 16 w
+// and on); 1: the split packing, whose 16-lane groups hold planet p in slots
+// 2p and 2p + 1 (both are written).
+template <int STORAGE> __device__ __forceinline__ int wide_slot(int w, int lane) {
+  const int k = w * WIDE_SLOTS + (lane >> 2);
+  return STORAGE == 1 ? 2 * k : k;
+}
+
+template <int G, bool GR, int SCHEME, int KC, int STORAGE>
+__device__ __forceinline__ void wide_group(const StepParams& p, int w, double* block, int lane) {
+  const int slot = wide_slot<STORAGE>(w, lane), c = wide_comp(lane), ns = p.ns;
+  double* st = p.st + (size_t)c * ns + slot;
+  const size_t r3 = (size_t)3 * ns;
+  WideLane L;
+  L.q = st[0];
+  L.v = st[r3];
+  L.cq = st[2 * r3 + ns];
+  L.cv = st[3 * r3 + ns];
+  L.m = p.st[(size_t)6 * ns + slot];
+  L.m0 = p.m0s[slot];
+  L.dt = p.dts[slot];
+  L.sys = p.slot_sys[slot];
+  L.pl = p.slot_pl[slot];
+  L.first = L.sys >= 0 ? p.synced[L.sys] : 1;
+  wide_steps<G, GR, SCHEME, KC>(p, L, block, lane);
+  if ((lane & 3) < 3) {
+    st[0] = L.q;
+    st[r3] = L.v;
+    st[2 * r3 + ns] = L.cq;
+    st[3 * r3 + ns] = L.cv;
+    if (STORAGE == 1) {
+      st[1] = L.q;
+      st[r3 + 1] = L.v;
+      st[2 * r3 + ns + 1] = L.cq;
+      st[3 * r3 + ns + 1] = L.cv;
+    }
+  }
+}
+
+// Recording a segment of reverse mode (adj_record_lane of wh.hip, whose tape
+// rows it writes): the checkpoint's state through n_rec steps.  Lanes 0..2 of
+// a planet write the rows of their component, lane 3 the anomaly; in the split
+// packing's storage both of a planet's slots, adjacent, take the value.
+template <int STORAGE> __device__ __forceinline__ void wide_put(double* row, double x) {
+  if (STORAGE == 1) *(double2*)row = make_double2(x, x);
+  else *row = x;
+}
+
+template <int G, bool GR, int SCHEME, int STORAGE>
+__device__ __forceinline__ void wide_record(const StepParams& p, const double* ck, double* tape, int n_rec,
+                                            bool first_synced, int w, double* block, int lane) {
+  const int slot = wide_slot<STORAGE>(w, lane), c = wide_comp(lane), ns = p.ns;
+  const size_t r3 = (size_t)3 * ns, step_rows = (size_t)wh_host::WH_TAPE_ROWS * ns;
+  const double* cs = ck + (size_t)c * ns + slot;
+  WideLane L{};
+  L.q = cs[0];
+  L.v = cs[r3];
+  L.cq = cs[2 * r3];
+  L.cv = cs[3 * r3];
+  L.m = p.st[(size_t)6 * ns + slot];
+  L.m0 = p.m0s[slot];
+  const double dt = p.dts[slot], h = 0.5 * dt;
+  const double inv_m0 = 1.0 / L.m0;
+  const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
+  const bool comp = (lane & 3) < 3;
+  WideKick<G> wk;
+  wk.init(block, lane, L.m);
+  KepNoDiag dg;
+  double vk;
+  double* row = tape + (size_t)c * ns + slot;         // the lane's rows: c, 3 + c, 7 + c
+  double* xrow = tape + (size_t)6 * ns + slot;
+  auto put_state = [&]() {
+    if (comp) { wide_put<STORAGE>(row, L.q); wide_put<STORAGE>(row + r3, L.v); }
+  };
+  auto put_rest = [&](double X) {
+    if (comp) wide_put<STORAGE>(row + 2 * r3 + ns, vk);
+    else wide_put<STORAGE>(xrow, X);
+    row += step_rows;
+    xrow += step_rows;
+  };
+  if constexpr (SCHEME == SCHEME_SABA) {
+    const int nu = p.saba_n;
+    const double c1dt = p.sc[0] * dt;
+    for (int s = 0; s < n_rec; ++s)
+      for (int k = 0; k < nu; ++k) {
+        const double tau = k > 0 ? p.sc[k] * dt : (first_synced && s == 0 ? c1dt : 2.0 * c1dt);
+        const double tb = p.sd[k] * dt;
+        put_state();
+        const double X = wide_drift<0>(L, tau, dg);
+        wide_kick<G, false>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
+        put_rest(X);
+      }
+  } else if constexpr (SCHEME == WH_KDK) {
+    double ta = first_synced ? 0.0 : h;
+    double ti = first_synced ? h : dt;
+    for (int s = 0; s < n_rec; ++s) {
+      put_state();
+      wide_kick<G, GR>(L, wk, inv_m0, kg, ta, ti, h, vk);
+      ta = h;
+      ti = dt;
+      put_rest(wide_drift<0>(L, dt, dg));
+    }
+  } else {
+    double tk = first_synced ? h : dt;
+    for (int s = 0; s < n_rec; ++s) {
+      put_state();
+      const double X = wide_drift<0>(L, tk, dg);
+      tk = dt;
+      wide_kick<G, GR>(L, wk, inv_m0, kg, h, dt, h, vk);
+      put_rest(X);
+    }
+  }
+}
+
+// The persistent step kernel of this form, defined and instantiated in
+// wh_wide_step.hip.  Up to four wavefronts per workgroup.
+template <bool GR, int SCHEME, int KC, int STORAGE>
+__global__ __launch_bounds__(256) void k_step_wide(StepParams p);
+
+}  // namespace wh
