@@ -185,8 +185,9 @@ __device__ __forceinline__ void kick_block(Lane& L, const Exch<G, EXCH>& ex, dou
   if (GR) {
     ex.momentum(L.m, L.vx, L.vy, L.vz, sx, sy, sz);
     double k1 = ta * inv_m0;
-    L.cqx = fma(k1, sx, L.cqx); L.cqy = fma(k1, sy, L.cqy); L.cqz = fma(k1, sz, L.cqz);
-    const double qx = fma(k1, sx, L.qx), qy = fma(k1, sy, L.qy), qz = fma(k1, sz, L.qz);
+    double dqx = k1 * sx, dqy = k1 * sy, dqz = k1 * sz;
+    L.cqx += dqx; L.cqy += dqy; L.cqz += dqz;
+    double qx = L.qx + dqx, qy = L.qy + dqy, qz = L.qz + dqz;
     ex.accel(qx, qy, qz, L.m, ax, ay, az);
     double gx, gy, gz;
     gr_accel(qx, qy, qz, kg, gx, gy, gz);
@@ -194,11 +195,12 @@ __device__ __forceinline__ void kick_block(Lane& L, const Exch<G, EXCH>& ex, dou
   } else {
     ex.accel(L.qx, L.qy, L.qz, L.m, ax, ay, az);
   }
-  L.cvx = fma(ti, ax, L.cvx); L.cvy = fma(ti, ay, L.cvy); L.cvz = fma(ti, az, L.cvz);
-  vkx = fma(ti, ax, L.vx); vky = fma(ti, ay, L.vy); vkz = fma(ti, az, L.vz);
+  double dvx = ti * ax, dvy = ti * ay, dvz = ti * az;
+  L.cvx += dvx; L.cvy += dvy; L.cvz += dvz;
+  vkx = L.vx + dvx; vky = L.vy + dvy; vkz = L.vz + dvz;
   ex.momentum(L.m, vkx, vky, vkz, sx, sy, sz);
   double k2 = (GR ? tc : ta + tc) * inv_m0;
-  L.cqx = fma(k2, sx, L.cqx); L.cqy = fma(k2, sy, L.cqy); L.cqz = fma(k2, sz, L.cqz);
+  L.cqx += k2 * sx; L.cqy += k2 * sy; L.cqz += k2 * sz;
   renorm_all(L);
 }
 
@@ -349,20 +351,19 @@ __device__ __forceinline__ void step_lane(const StepParams& p, Lane& L, int lane
     JacConst jc{};
     if constexpr (JAC) jc = jac_const<G>(L.m0, L.m, pg);
     const double mu = JAC ? jc.Mi : L.m0;
-    // One loop over the n K-B units of a step; unrolled by k, the kernel
-    // held several copies of the body and a register set for each path.
     const double c1dt = p.sc[0] * dt;
-    const double sc1 = p.sc[1], sc2 = p.sc[2], sc3 = p.sc[3], sd0 = p.sd[0], sd1 = p.sd[1], sd2 = p.sd[2], sd3 = p.sd[3];
     double tk = L.first ? c1dt : 2.0 * c1dt;
-    const int n_units = p.saba_n, n_steps = p.n_steps;
-    for (int s = 0; s < n_steps; ++s) {
-#pragma unroll 1
-      for (int k = 0; k < n_units; ++k) {
-        drift(L, mu, tk, dg);
-        const double tb = (k == 0 ? sd0 : k == 1 ? sd1 : k == 2 ? sd2 : sd3) * dt;
-        if constexpr (JAC) kick_jacobi<G, EXCH, GR>(L, ex, jc, pg, tb, vkx, vky, vkz, kg);
-        else kick_block<G, false, EXCH>(L, ex, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vkx, vky, vkz);
-        tk = k + 1 < n_units ? (k == 0 ? sc1 : k == 1 ? sc2 : sc3) * dt : 2.0 * c1dt;
+    for (int s = 0; s < p.n_steps; ++s) {
+      drift(L, mu, tk, dg);
+      tk = 2.0 * c1dt;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (k < p.saba_n) {
+          const double tb = p.sd[k] * dt;
+          if constexpr (JAC) kick_jacobi<G, EXCH, GR>(L, ex, jc, pg, tb, vkx, vky, vkz, kg);
+          else kick_block<G, false, EXCH>(L, ex, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vkx, vky, vkz);
+          if (k + 1 < p.saba_n) drift(L, mu, p.sc[k + 1] * dt, dg);
+        }
       }
     }
   } else if constexpr (JAC) {
@@ -400,7 +401,14 @@ __device__ __forceinline__ void step_lane(const StepParams& p, Lane& L, int lane
       drift<KC>(L, L.m0, dt, dg);
     }
   }
-  int f = lane_flags(L, dg, p.zlim);
+  int f = 0;
+  if (L.pl >= 0) {
+    bool fin = __builtin_isfinite(L.qx) && __builtin_isfinite(L.qy) && __builtin_isfinite(L.qz) &&
+               __builtin_isfinite(L.vx) && __builtin_isfinite(L.vy) && __builtin_isfinite(L.vz);
+    if (!fin) f |= WH_F_NONFINITE;
+    if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
+    if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
+  }
   f = group_or<G>(f);
   if ((lane & (G - 1)) == 0 && L.sys >= 0) {
     p.flags[L.sys] |= (uint32_t)f;
@@ -795,7 +803,7 @@ __device__ void apply_corrector(const StepParams& p, Lane& L, int lane, bool inv
   Exch<G, 0> ex;
   ex.init(lane, L.m);
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepNoDiag dg;
+  KepDiag dg{0.0, 1.0e300};
   double vkx, vky, vkz;
   const double h = L.dt;
 #pragma unroll
@@ -835,7 +843,7 @@ __device__ void corrector_run(const StepParams& p, Lane& L, int lane, bool inver
   Exch<G, 0> ex;
   ex.init(lane, L.m);
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepNoDiag dg;
+  KepDiag dg{0.0, 1.0e300};
   double vkx, vky, vkz;
   for (int j = 0; j < n_sub; ++j) {
     double tau;
@@ -850,7 +858,7 @@ __device__ void sync_lane(const StepParams& p, Lane& L, int lane) {
   if (!L.first) {   // uniform over the group: one system, one flag
     const double h = 0.5 * L.dt;
     if (SCHEME == WH_DKD || SCHEME == SCHEME_SABA) {
-      KepNoDiag dg;
+      KepDiag dg{0.0, 1.0e300};
       const double tau = SCHEME == SCHEME_SABA ? p.sc[0] * L.dt : h;
       double mu = L.m0;
       if constexpr (JAC) mu = jac_const<G>(L.m0, L.m, pg).Mi;
@@ -996,7 +1004,7 @@ template <bool GR, int SCHEME> __device__ void sync_group_mixed(const SyncParams
   if (!L.first) {
     const double h = 0.5 * L.dt;
     if (SCHEME == WH_DKD) {
-      KepNoDiag dg;
+      KepDiag dg{0.0, 1.0e300};
       drift(L, L.m0, h, dg);
     } else {
       double vkx, vky, vkz;
@@ -1109,7 +1117,7 @@ template <int G, bool GR, int SCHEME> __device__ void sync_group_pair(const Sync
   if (!A.first) {
     const double h = 0.5 * A.dt;
     if (SCHEME == WH_DKD || SCHEME == SCHEME_SABA) {
-      KepNoDiag dg;
+      KepDiag dg{0.0, 1.0e300};
       const double tau = SCHEME == SCHEME_SABA ? p.sc[0] * A.dt : h;
       drift(A, A.m0, tau, dg);
       drift(B, B.m0, tau, dg);
@@ -1340,7 +1348,7 @@ __device__ void adj_record_lane(const AdjParams& q, int slot, int lane) {
   const double dt = L.dt, h = 0.5 * dt;
   const double inv_m0 = 1.0 / L.m0;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepNoDiag dg;
+  KepDiag dg{0.0, 1.0e300};
   if constexpr (SCH == SCHEME_SABA) {
     // SABA_n: n units per step, unit k = K(tau_k) then the perturbation kick
     // B(d_k dt); tau_0 = c_1 dt (2 c_1 dt after the first step), tau_k = c_{k+1} dt
@@ -1570,7 +1578,7 @@ __device__ void adj_record_pair(const AdjParams& q, int sa) {
   const double dt = p.dts[sa], h = 0.5 * dt;
   const double inv_m0 = 1.0 / A.m0;
   const double kg = GR ? p.kgr * A.m0 * A.m0 : 0.0;
-  KepNoDiag dga, dgb;
+  KepDiag dga{0.0, 1.0e300}, dgb{0.0, 1.0e300};
   if constexpr (SCH == SCHEME_SABA) {
     const int nu = p.saba_n;
     const double c1dt = p.sc[0] * dt;
@@ -2154,7 +2162,7 @@ __device__ void adj_record_jac(const AdjParams& q, int slot, int lane) {
   const JacConst jc = jac_const<G>(L.m0, L.m, pg);
   const double dt = p.dts[slot], h = 0.5 * dt;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  KepNoDiag dg;
+  KepDiag dg{0.0, 1.0e300};
   auto put_state = [&](double* row) {
     row[0] = L.qx; row[ns] = L.qy; row[2 * ns] = L.qz;
     row[3 * ns] = L.vx; row[4 * ns] = L.vy; row[5 * ns] = L.vz;
@@ -2301,7 +2309,7 @@ __device__ void corrector_vjp(const StepParams& p, const Lane& L0, int lane, boo
     double tau;
     if (corrector_substep(p, j, inverse, L0.dt, tau)) {
       Lane Lx = L;
-      KepNoDiag dg;
+      KepDiag dg{0.0, 1.0e300};
       const double X = drift(Lx, jc.Mi, tau, dg);
       KepFwd k;
       jac_drift_vjp(a, gMim1, jc.Mi, L.qx, L.qy, L.qz, L.vx, L.vy, L.vz, tau, X, k);
@@ -2336,7 +2344,7 @@ template <int G, bool GR, int SCH> __device__ void adj_init_jac_lane(const AdjPa
   const double x0x = L.qx, x0y = L.qy, x0z = L.qz, v0x = L.vx, v0y = L.vy, v0z = L.vz;
   double tau = 0.0, X = 0.0;
   if (!synced) {
-    KepNoDiag dg;
+    KepDiag dg{0.0, 1.0e300};
     if (SCH == WH_KDK) {
       double vkx, vky, vkz;
       kick_jacobi<G, 1, GR>(L, ex, jc, pg, 0.5 * dt, vkx, vky, vkz, kg);
@@ -2437,7 +2445,7 @@ __global__ void k_adj_init(AdjParams q, int synced) {
       double vx = q.ck[3 * ns + slot], vy = q.ck[4 * ns + slot], vz = q.ck[5 * ns + slot];
       // the pending drift: K(dt/2), or K(c_1 dt) for SABA_n
       double m0 = p.m0s[slot], h = p.saba_n > 0 ? p.sc[0] * p.dts[slot] : 0.5 * p.dts[slot];
-      KepNoDiag dg;
+      KepDiag dg{0.0, 1.0e300};
       KepCoef kc;
       double X = kepler_coeffs<KEP_NH, KEP_NN, KEP_KH, KEP_KN>(qx, qy, qz, vx, vy, vz, m0, h, dg, kc);
       KepFwd k;
@@ -2938,12 +2946,13 @@ void launch_wide(const wh_ctx* c, const StepParams& p, hipStream_t st) {
 // Whether the step runs with four lanes per planet: in the one-planet and
 // split packings of a DHC context with the DPP exchange, while its
 // wavefronts (four times the one-planet packing's, twice the split packing's)
-// are no more than the GPU has SIMDs.  Eight-planet systems without GR, us per
-// step with and without it: one system 0.63 and 0.91 (split packing 0.62 and
-// 0.74), 2048 systems, a wavefront per SIMD, 0.71 and 0.92 (0.71 and 0.75); at
-// 3072, 1.5 per SIMD, it would take 1.12 against 0.92.  Four planets: 4096
-// systems 0.62 and 0.71, 8192 systems 1.06 and 0.72; two planets: 8192 systems
-// 0.54 and 0.62, 16384 systems 0.98 and 0.63.
+// are no more than the GPU has SIMDs: there the wavefront's own instructions
+// set the time, beyond it the sum of all.  Eight-planet systems without GR, us
+// per step with and without it: one system 0.66 and 0.95 (split packing 0.67
+// and 0.78), 2048 systems, a wavefront per SIMD, 0.74 and 0.97 (0.77 and 0.80);
+// at 3072, 1.5 per SIMD, it would take 1.12 against 0.96.  Four planets: 4096
+// systems 0.65 and 0.75, 8192 systems 1.06 and 0.78; two planets: 8192 systems
+// 0.58 and 0.65, 16384 systems 0.98 and 0.67.
 wh_status choose_wide(wh_ctx* c) {
   c->wide_waves = 0;
   if (c->cfg.coords != WH_COORDS_DHC || c->P.pair || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP)

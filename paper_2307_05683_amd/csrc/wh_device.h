@@ -158,13 +158,6 @@ template <int K, int N0> __device__ __forceinline__ double stumpff_series(double
 struct KepDiag {
   double zmax;   // largest Stumpff argument of a final evaluation
   double bmin;   // smallest beta = 2 mu / r0 - v^2 (<= 0: unbound)
-  __device__ __forceinline__ void see_beta(double beta) { bmin = fmin(bmin, beta); }
-  __device__ __forceinline__ void see_z(double z) { zmax = fmax(zmax, z); }
-};
-// Where nothing reads them (the reverse pass, synchronized copies).
-struct KepNoDiag {
-  __device__ __forceinline__ void see_beta(double) {}
-  __device__ __forceinline__ void see_z(double) {}
 };
 
 // Lagrange coefficients of a Kepler drift: the drift maps (Q, V) to
@@ -174,87 +167,17 @@ struct KepCoef {
   double fm1, g, fd, gdm1;
 };
 
-// Kepler drift of one planet over tau about a star with mu = G m0 (Sec. 3.2),
-// in universal variables: with r0 = |Q|, eta = Q.V, beta = 2mu/r0 - V^2,
-// zeta = mu - beta r0, solve
-//   F(X) = r0 X + eta G2(X) + zeta G3(X) - tau = 0,  G_n = X^n c_n(beta X^2),
-// with NH Halley steps on KH series terms, then NN Newton steps on KN terms,
-// no convergence test and no branch on the data, then form the Lagrange
-// coefficients.  Initial guess: X = tau/r0 - eta tau^2 / (2 r0^3).  G0 and G1
-// come from G_n = X^n/n! - beta G_{n+2}: one multiplication fewer per
-// iteration than c0 = 1 - z c2 and c1 = 1 - z c3, and X rounds once less.  F
-// adds r0 X before eta G2, so that G2's term rounds at the size of what is
-// left of r0 X - tau.  Error of the drift's increment against 113 bits, 3e5
-// solves, e < 0.05 at P/20: median 5.75e-17 of the orbit's size, 5.97e-17 with
-// c0, c1 and r0 X added last; e up to 0.8 and steps from P/60 to P/4 gain the
-// same 4%.  g' - 1 is taken from the Wronskian identity
-// f g' - f' g = 1, which keeps the discrete map area-preserving to rounding.
-// Returns the anomaly X.
-template <int NH, int NN, int KH, int KN, class D>
-__device__ __forceinline__ double kepler_coeffs(double qx, double qy, double qz, double vx, double vy, double vz,
-                                                double mu, double tau, D& dg, KepCoef& k) {
-  static_assert(NH >= 0 && NN >= 1, "the last step is a Newton step");
-  const double r2 = fma(qx, qx, fma(qy, qy, qz * qz));
-  const double v2 = fma(vx, vx, fma(vy, vy, vz * vz));
-  const double eta = fma(qx, vx, fma(qy, vy, qz * vz));
-  const double ir0 = rsqrt_full(r2);
-  const double r0 = r2 * ir0;
-  const double mi = mu * ir0;
-  const double beta = fma(2.0, mi, -v2);
-  const double zeta = fma(-beta, r0, mu);
-  dg.see_beta(beta);
-  const double a = tau * ir0;
-  double X = a * fma(-0.5 * eta * ir0, a, 1.0);
-#pragma unroll
-  for (int it = 0; it < NH; ++it) {
-    const double X2 = X * X;
-    const double z = beta * X2;
-    const double G2 = X2 * stumpff_series<KH, 2>(z), G3 = X * (X2 * stumpff_series<KH, 3>(z));
-    const double G0 = fma(-beta, G2, 1.0), G1 = fma(-beta, G3, X);
-    const double F = fma(eta, G2, fma(r0, X, fma(zeta, G3, -tau)));
-    const double Fp = fma(eta, G1, fma(zeta, G2, r0));
-    const double Fpp = fma(eta, G0, zeta * G1);
-    // Halley: X -= 2 F F' / (2 F'^2 - F F'')
-    const double den = fma(-0.5 * F, Fpp, Fp * Fp);
-    X = fma(-F * Fp, rcp_seed(den), X);
-  }
-  // Newton steps.  The G functions of the final anomaly come from those of
-  // the last iterate: G_n(X + d) = G_n(X) + d G_{n-1}(X) + O(d^2), and d is at
-  // rounding level once the iteration has converged.
-  double G1 = 0.0, G2 = 0.0, G3 = 0.0;
-#pragma unroll
-  for (int it = 0; it < NN; ++it) {
-    const double X2 = X * X;
-    const double z = beta * X2;
-    if (it == NN - 1) dg.see_z(z);
-    G2 = X2 * stumpff_series<KN, 2>(z);
-    G3 = X * (X2 * stumpff_series<KN, 3>(z));
-    G1 = fma(-beta, G3, X);
-    const double F = fma(eta, G2, fma(r0, X, fma(zeta, G3, -tau)));
-    const double Fp = fma(eta, G1, fma(zeta, G2, r0));
-    const double d = -F * rcp_seed(Fp);
-    X += d;
-    if (it == NN - 1) {
-      const double G0 = fma(-beta, G2, 1.0);
-      G3 = fma(d, G2, G3);
-      G2 = fma(d, G1, G2);
-      G1 = fma(d, G0, G1);
-    }
-  }
-  const double r = fma(zeta, G2, fma(eta, G1, r0));
-  const double ir = rcp_full(r);
-  k.fm1 = -mi * G2;
-  k.g = fma(-mu, G3, tau);
-  k.fd = -(mi * ir) * G1;
-  k.gdm1 = fma(k.fd, k.g, -k.fm1) * rcp_full(1.0 + k.fm1);
-  return X;
-}
+// Iteration counts of the fixed Kepler solve: NH Halley steps with KH series
+// terms, then NN Newton steps with KN terms.  KepCountsFixed bakes them in at
+// compile time (the integrator); KepCountsRun takes them at run time, uniform
+// over a launch (the envelope explorer of App. A).
+template <int NH, int NN, int KH, int KN> struct KepCountsFixed {
+  __device__ static constexpr int nh() { return NH; }
+  __device__ static constexpr int nn() { return NN; }
+  template <int N0> __device__ static double series_h(double z) { return stumpff_series<KH, N0>(z); }
+  template <int N0> __device__ static double series_n(double z) { return stumpff_series<KN, N0>(z); }
+};
 
-// ---------------------------------------------------------------------------
-// The explorer's solve (App. A): the same method with counts and series
-// lengths that a launch chooses.  Its relative a-error is a difference at
-// rounding level, so it keeps its own order of operations and its maps their
-// bits, whatever the integrator's solve above does.
 // 1/n! for n = 0..31 (exact to n = 18, correctly rounded products beyond).
 struct InvFactTable {
   double v[32];
@@ -291,11 +214,18 @@ struct KepCountsRun {
   template <int N0> __device__ double series_n(double z) const { return stumpff_series_rt<N0>(z, kn); }
 };
 
-// Counts from P; with no Newton step the G functions are evaluated afresh at
-// the last Halley iterate.
-template <class P, class D>
+// Kepler drift of one planet over tau about a star with mu = G m0 (Sec. 3.2),
+// in universal variables: with r0 = |Q|, eta = Q.V, beta = 2mu/r0 - V^2,
+// zeta = mu - beta r0, solve
+//   F(X) = r0 X + eta G2(X) + zeta G3(X) - tau = 0,  G_n = X^n c_n(beta X^2),
+// with a fixed number of Halley steps then Newton steps (counts and series
+// lengths from P), no convergence test and no branch on the data, then form
+// the Lagrange coefficients.  Initial guess: X = tau/r0 - eta tau^2 / (2 r0^3).
+// g' - 1 is taken from the Wronskian identity f g' - f' g = 1, which keeps
+// the discrete map area-preserving to rounding.  Returns the anomaly X.
+template <class P>
 __device__ __forceinline__ double kepler_coeffs_p(const P& p, double qx, double qy, double qz, double vx, double vy,
-                                                  double vz, double mu, double tau, D& dg, KepCoef& k) {
+                                                  double vz, double mu, double tau, KepDiag& dg, KepCoef& k) {
   double r2 = fma(qx, qx, fma(qy, qy, qz * qz));
   double v2 = fma(vx, vx, fma(vy, vy, vz * vz));
   double eta = fma(qx, vx, fma(qy, vy, qz * vz));
@@ -303,7 +233,7 @@ __device__ __forceinline__ double kepler_coeffs_p(const P& p, double qx, double 
   double r0 = r2 * ir0;
   double beta = fma(2.0 * mu, ir0, -v2);
   double zeta = fma(-beta, r0, mu);
-  dg.see_beta(beta);
+  dg.bmin = fmin(dg.bmin, beta);
   double a = tau * ir0;
   double X = a * fma(-0.5 * eta * ir0, a, 1.0);
 #pragma unroll
@@ -330,7 +260,7 @@ __device__ __forceinline__ double kepler_coeffs_p(const P& p, double qx, double 
   for (int it = 0; it < p.nn(); ++it) {
     double X2 = X * X;
     double z = beta * X2;
-    if (it == p.nn() - 1) dg.see_z(z);
+    if (it == p.nn() - 1) dg.zmax = fmax(dg.zmax, z);
     double c2 = p.template series_n<2>(z);
     double c3 = p.template series_n<3>(z);
     double c1 = fma(-z, c3, 1.0);
@@ -351,7 +281,7 @@ __device__ __forceinline__ double kepler_coeffs_p(const P& p, double qx, double 
     // Halley iterate with the final series length
     double X2 = X * X;
     double z = beta * X2;
-    dg.see_z(z);
+    dg.zmax = fmax(dg.zmax, z);
     double c2 = p.template series_n<2>(z);
     double c3 = p.template series_n<3>(z);
     G1 = X * fma(-z, c3, 1.0); G2 = X2 * c2; G3 = X2 * X * c3;
@@ -365,31 +295,37 @@ __device__ __forceinline__ double kepler_coeffs_p(const P& p, double qx, double 
   return X;
 }
 
-// One coordinate of the compensated state under the linear map of a drift:
-// (x, cx) <- (1 + a) x + b y of the two coordinates' rounded values, with the
-// rounding errors of both terms and the image of the low parts, a cx + b cy,
-// in cx.
-//   t = x + a x in one FMA; its error x - t + a x is exact, |a x| < |x|
-//     (a = f - 1 or g' - 1, -0.05 for twenty steps an orbit);
-//   s = t + b y: the two-sum of t and the rounded product p = b y, its last
-//     difference p - bp replaced by fma(b, y, -bp), which brings p's own
-//     rounding error with it.  s must come from the rounded p: the two-sum's
-//     differences are exact for two doubles.
-// Fourteen instructions; forming the increment a x + b y first and adding it
-// by a two-sum took sixteen and lost a x's error where |b y| < |a x| (against
-// 113 bits, 4e6 random coordinates: rms 7.6e-19 of the larger term, now
-// 7e-33).  Contraction is off: fusing b y into a sum would count the
-// product's error twice.
-__device__ __forceinline__ void linear_dd(double a, double& x, double& cx, double b, double y, double cy) {
+template <int NH, int NN, int KH, int KN>
+__device__ __forceinline__ double kepler_coeffs(double qx, double qy, double qz, double vx, double vy, double vz,
+                                                double mu, double tau, KepDiag& dg, KepCoef& k) {
+  return kepler_coeffs_p(KepCountsFixed<NH, NN, KH, KN>{}, qx, qy, qz, vx, vy, vz, mu, tau, dg, k);
+}
+
+// Increment a x + b y of one coordinate as an unevaluated sum hi + lo, with
+// the rounding errors of the product b y and of the sum kept in lo (b y is
+// the larger term: g V for positions, f' Q for velocities).  Contraction is
+// off: fusing b*y into p - t would count the product error twice.
+__device__ __forceinline__ void lin2_dd(double a, double x, double b, double y, double& hi, double& lo) {
 #pragma clang fp contract(off)
-  const double t = fma(a, x, x);
-  const double te = fma(a, x, x - t);
-  const double p = b * y;
-  const double s = t + p;
-  const double bp = s - t;
-  const double se = (t - (s - bp)) + fma(b, y, -bp);
-  cx = fma(a, cx, fma(b, cy, (cx + te) + se));
-  x = s;
+  double p = b * y;
+  double pe = fma(b, y, -p);
+  double t = fma(a, x, p);
+  double te = fma(a, x, p - t);
+  hi = t;
+  lo = pe + te;
+}
+
+// Double-double accumulation (s, c) += (d, e), where s + c is the state with
+// |c| <= ulp(s)/2: an exact two-sum of s and d, the low parts added, then
+// renormalized.
+__device__ __forceinline__ void dd_add(double& s, double& c, double d, double e) {
+#pragma clang fp contract(off)
+  double t = s + d;
+  double bp = t - s;
+  double err = (s - (t - bp)) + (d - bp);
+  double lo = (c + e) + err;
+  s = t + lo;
+  c = lo - (s - t);
 }
 
 // The paper's solver: 2 Halley steps with 4 series terms, 2 Newton steps
@@ -551,25 +487,20 @@ template <int G> __device__ __forceinline__ void interaction_accel_dpp(const Dpp
 
 // Jump (Sec. 3.4): every planet of the group moves by (tau/m0) sum_j m_j V_j;
 // velocities are unchanged.  Returns the group's total planetary momentum.
-// Contraction is off, so that every lane sums the same rounded products.
 template <int G> __device__ __forceinline__ void group_momentum(double m, double vx, double vy, double vz,
                                                                 double& sx, double& sy, double& sz) {
-#pragma clang fp contract(off)
   sx = group_sum<G>(m * vx);
   sy = group_sum<G>(m * vy);
   sz = group_sum<G>(m * vz);
 }
 
 // GR acceleration -6 mu^2/c^2 * Q/|Q|^4, from the potential -3 mu^2 m/(c^2 |Q|^2)
-// centred on the star, as the factor of Q.  kg = 6 mu^2 / c^2.
-__device__ __forceinline__ double gr_weight(double qx, double qy, double qz, double kg) {
-  double r2 = fma(qx, qx, fma(qy, qy, qz * qz));
-  double ir2 = rcp_full(r2);
-  return -kg * ir2 * ir2;
-}
+// centred on the star.  kg = 6 mu^2 / c^2.
 __device__ __forceinline__ void gr_accel(double qx, double qy, double qz, double kg, double& ax, double& ay,
                                          double& az) {
-  const double w = gr_weight(qx, qy, qz, kg);
+  double r2 = fma(qx, qx, fma(qy, qy, qz * qz));
+  double ir2 = rcp_full(r2);
+  double w = -kg * ir2 * ir2;
   ax = w * qx;
   ay = w * qy;
   az = w * qz;

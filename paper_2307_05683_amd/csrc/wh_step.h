@@ -119,32 +119,60 @@ __device__ __forceinline__ void store_lane(const StepParams& p, int slot, const 
 }
 
 // The state of a coordinate is the unevaluated sum s + c (rounded value and
-// compensation).  Operators read the rounded values.  A Kepler drift maps s
-// and c together (linear_dd): what rounding drops from the new s goes to c;
-// kicks and jumps add their (small) increments to c; one renormalization per
-// step moves c back to at most half an ulp of s.
+// compensation).  Operators read the rounded values.  A Kepler drift adds
+// its increment to s by an exact two-sum and sends the two-sum's error, the
+// increment's own low part and the image of c under the drift to c; kicks and
+// jumps add their (small) increments to c; one renormalization per step
+// moves c back to at most half an ulp of s.
+__device__ __forceinline__ void two_sum(double a, double b, double& s, double& e) {
+#pragma clang fp contract(off)
+  s = a + b;
+  double bp = s - a;
+  e = (a - (s - bp)) + (b - bp);
+}
 __device__ __forceinline__ void renorm(double& s, double& c) {
 #pragma clang fp contract(off)
   double t = s + c;
   c = c - (t - s);
   s = t;
 }
+__device__ __forceinline__ void add_hi(double& s, double& c, double h, double l) {
+#pragma clang fp contract(off)
+  double t, e;
+  two_sum(s, h, t, e);
+  s = t;
+  c = (c + l) + e;
+}
+
 // Kepler drift K(tau) of the compensated state.  The coefficients come from
-// the rounded values; (Q, V) -> (f Q + g V, f' Q + g' V) acts on value and
-// compensation of each coordinate (linear_dd).  Returns the anomaly X.
+// the rounded values; the increment (f-1)Q + gV, f'Q + (g'-1)V is formed in
+// double-double (lin2_dd) and c is carried through the same linear map.
+// Returns the anomaly X.
 // KC selects the iteration counts of the solve (KepSet, wh_device.h).
-template <int KC = 0, class D>
-__device__ __forceinline__ double drift(Lane& L, double mu, double tau, D& dg) {
+template <int KC = 0>
+__device__ __forceinline__ double drift(Lane& L, double mu, double tau, KepDiag& dg) {
   KepCoef k;
   double X = kepler_coeffs<KepSet<KC>::NH, KepSet<KC>::NN, KepSet<KC>::KH, KepSet<KC>::KN>(L.qx, L.qy, L.qz, L.vx,
                                                                                           L.vy, L.vz, mu, tau, dg, k);
-  const Lane O = L;   // both halves of the map read the state before it
-  linear_dd(k.fm1, L.qx, L.cqx, k.g, O.vx, O.cvx);
-  linear_dd(k.fm1, L.qy, L.cqy, k.g, O.vy, O.cvy);
-  linear_dd(k.fm1, L.qz, L.cqz, k.g, O.vz, O.cvz);
-  linear_dd(k.gdm1, L.vx, L.cvx, k.fd, O.qx, O.cqx);
-  linear_dd(k.gdm1, L.vy, L.cvy, k.fd, O.qy, O.cqy);
-  linear_dd(k.gdm1, L.vz, L.cvz, k.fd, O.qz, O.cqz);
+  double hqx, hqy, hqz, hvx, hvy, hvz, lqx, lqy, lqz, lvx, lvy, lvz;
+  lin2_dd(k.fm1, L.qx, k.g, L.vx, hqx, lqx);
+  lin2_dd(k.fm1, L.qy, k.g, L.vy, hqy, lqy);
+  lin2_dd(k.fm1, L.qz, k.g, L.vz, hqz, lqz);
+  lin2_dd(k.gdm1, L.vx, k.fd, L.qx, hvx, lvx);
+  lin2_dd(k.gdm1, L.vy, k.fd, L.qy, hvy, lvy);
+  lin2_dd(k.gdm1, L.vz, k.fd, L.qz, hvz, lvz);
+  lqx = fma(k.fm1, L.cqx, fma(k.g, L.cvx, lqx));
+  lqy = fma(k.fm1, L.cqy, fma(k.g, L.cvy, lqy));
+  lqz = fma(k.fm1, L.cqz, fma(k.g, L.cvz, lqz));
+  lvx = fma(k.fd, L.cqx, fma(k.gdm1, L.cvx, lvx));
+  lvy = fma(k.fd, L.cqy, fma(k.gdm1, L.cvy, lvy));
+  lvz = fma(k.fd, L.cqz, fma(k.gdm1, L.cvz, lvz));
+  add_hi(L.qx, L.cqx, hqx, lqx);
+  add_hi(L.qy, L.cqy, hqy, lqy);
+  add_hi(L.qz, L.cqz, hqz, lqz);
+  add_hi(L.vx, L.cvx, hvx, lvx);
+  add_hi(L.vy, L.cvy, hvy, lvy);
+  add_hi(L.vz, L.cvz, hvz, lvz);
   return X;
 }
 
@@ -168,27 +196,31 @@ __device__ __forceinline__ void kick_block_pair(Lane& A, Lane& B, const PairMass
   if (GR) {
     pair_momentum<G>(A.m, A.vx, A.vy, A.vz, B.m, B.vx, B.vy, B.vz, sx, sy, sz);
     const double k1 = ta * inv_m0;
-    A.cqx = fma(k1, sx, A.cqx); A.cqy = fma(k1, sy, A.cqy); A.cqz = fma(k1, sz, A.cqz);
-    B.cqx = fma(k1, sx, B.cqx); B.cqy = fma(k1, sy, B.cqy); B.cqz = fma(k1, sz, B.cqz);
-    qax = fma(k1, sx, qax); qay = fma(k1, sy, qay); qaz = fma(k1, sz, qaz);
-    qbx = fma(k1, sx, qbx); qby = fma(k1, sy, qby); qbz = fma(k1, sz, qbz);
+    const double dqx = k1 * sx, dqy = k1 * sy, dqz = k1 * sz;
+    A.cqx += dqx; A.cqy += dqy; A.cqz += dqz;
+    B.cqx += dqx; B.cqy += dqy; B.cqz += dqz;
+    qax += dqx; qay += dqy; qaz += dqz;
+    qbx += dqx; qby += dqy; qbz += dqz;
   }
   double aax, aay, aaz, abx, aby, abz;
   accel_pair<G>(pm, A.m, B.m, qax, qay, qaz, qbx, qby, qbz, aax, aay, aaz, abx, aby, abz);
   if (GR) {
-    double w = gr_weight(qax, qay, qaz, kg);
-    aax = fma(w, qax, aax); aay = fma(w, qay, aay); aaz = fma(w, qaz, aaz);
-    w = gr_weight(qbx, qby, qbz, kg);
-    abx = fma(w, qbx, abx); aby = fma(w, qby, aby); abz = fma(w, qbz, abz);
+    double gx, gy, gz;
+    gr_accel(qax, qay, qaz, kg, gx, gy, gz);
+    aax += gx; aay += gy; aaz += gz;
+    gr_accel(qbx, qby, qbz, kg, gx, gy, gz);
+    abx += gx; aby += gy; abz += gz;
   }
-  A.cvx = fma(ti, aax, A.cvx); A.cvy = fma(ti, aay, A.cvy); A.cvz = fma(ti, aaz, A.cvz);
-  B.cvx = fma(ti, abx, B.cvx); B.cvy = fma(ti, aby, B.cvy); B.cvz = fma(ti, abz, B.cvz);
-  vka[0] = fma(ti, aax, A.vx); vka[1] = fma(ti, aay, A.vy); vka[2] = fma(ti, aaz, A.vz);
-  vkb[0] = fma(ti, abx, B.vx); vkb[1] = fma(ti, aby, B.vy); vkb[2] = fma(ti, abz, B.vz);
+  const double dvax = ti * aax, dvay = ti * aay, dvaz = ti * aaz;
+  const double dvbx = ti * abx, dvby = ti * aby, dvbz = ti * abz;
+  A.cvx += dvax; A.cvy += dvay; A.cvz += dvaz;
+  B.cvx += dvbx; B.cvy += dvby; B.cvz += dvbz;
+  vka[0] = A.vx + dvax; vka[1] = A.vy + dvay; vka[2] = A.vz + dvaz;
+  vkb[0] = B.vx + dvbx; vkb[1] = B.vy + dvby; vkb[2] = B.vz + dvbz;
   pair_momentum<G>(A.m, vka[0], vka[1], vka[2], B.m, vkb[0], vkb[1], vkb[2], sx, sy, sz);
   const double k2 = (GR ? tc : ta + tc) * inv_m0;
-  A.cqx = fma(k2, sx, A.cqx); A.cqy = fma(k2, sy, A.cqy); A.cqz = fma(k2, sz, A.cqz);
-  B.cqx = fma(k2, sx, B.cqx); B.cqy = fma(k2, sy, B.cqy); B.cqz = fma(k2, sz, B.cqz);
+  A.cqx += k2 * sx; A.cqy += k2 * sy; A.cqz += k2 * sz;
+  B.cqx += k2 * sx; B.cqy += k2 * sy; B.cqz += k2 * sz;
   renorm_all(A);
   renorm_all(B);
 }
@@ -217,17 +249,21 @@ __device__ __forceinline__ void step_lane_pair(const StepParams& p, Lane& A, Lan
   if constexpr (SCHEME == SCHEME_SABA) {
     // SABA_n as in step_lane, B = I and J together (DHC, no GR)
     const double c1dt = p.sc[0] * dt;
-    const double sc1 = p.sc[1], sc2 = p.sc[2], sc3 = p.sc[3], sd0 = p.sd[0], sd1 = p.sd[1], sd2 = p.sd[2], sd3 = p.sd[3];
     double tk = A.first ? c1dt : 2.0 * c1dt;
-    const int n_units = p.saba_n, n_steps = p.n_steps;
-    for (int s = 0; s < n_steps; ++s) {
-#pragma unroll 1
-      for (int k = 0; k < n_units; ++k) {
-        drift(A, A.m0, tk, dga);
-        drift(B, B.m0, tk, dgb);
-        const double tb = (k == 0 ? sd0 : k == 1 ? sd1 : k == 2 ? sd2 : sd3) * dt;
-        kick_block_pair<G, false>(A, B, pm, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vka, vkb);
-        tk = k + 1 < n_units ? (k == 0 ? sc1 : k == 1 ? sc2 : sc3) * dt : 2.0 * c1dt;
+    for (int s = 0; s < p.n_steps; ++s) {
+      drift(A, A.m0, tk, dga);
+      drift(B, B.m0, tk, dgb);
+      tk = 2.0 * c1dt;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (k < p.saba_n) {
+          const double tb = p.sd[k] * dt;
+          kick_block_pair<G, false>(A, B, pm, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vka, vkb);
+          if (k + 1 < p.saba_n) {
+            drift(A, A.m0, p.sc[k + 1] * dt, dga);
+            drift(B, B.m0, p.sc[k + 1] * dt, dgb);
+          }
+        }
       }
     }
   } else if (SCHEME == WH_DKD) {

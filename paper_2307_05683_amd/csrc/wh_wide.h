@@ -1,7 +1,7 @@
-// Four lanes per planet: how small ensembles run the one-planet step.  256
-// VALU instructions per lane-step on eight-planet groups without GR (one lane
-// per planet: 457; the split layout: 382), 282 with GR (505; 440), and 15 LDS
-// instructions.
+// Four lanes per planet: how small ensembles run the one-planet step and the
+// split layout's.  VALU instructions per lane-step on eight-planet groups,
+// without and with GR: 271 and 303, and 15 LDS instructions (one lane per
+// planet: 474 and 522); in the split layout's order 273 and 301 (399 and 451).
 //
 // An ensemble with few wavefronts leaves most SIMDs idle, and a step's time is
 // then the instructions one wavefront issues.  Here a wavefront runs 16 planet
@@ -11,8 +11,10 @@
 // increments, the momentum sum and the renormalization run once per lane
 // instead of three times, and every pair of a system is evaluated on a lane of
 // its own.  Each operation and each order of summation is that of the
-// one-planet step (wh_device.h, kick_block), so the results are the same bits
-// and the two mix freely (reverse mode's recording, the per-size path).
+// packing's own step (drift, kick_block, group_momentum, interaction_accel_dpp
+// or accel_split, with the products that the compiler fuses there fused here),
+// so the results are the same bits and the forms mix freely: reverse mode's
+// recording, the per-size path, batches of either size.
 //
 // Exchange goes through LDS, 2 KiB per wavefront.  A wavefront's own LDS
 // operations stay in order, so writing and reading need no wait between them,
@@ -22,14 +24,7 @@
 //      partner's position;
 //   2. it evaluates 1/r^3 of its pair, writes it, and reads those of its
 //      planet's pairs;
-//   3. it adds the pairs' accelerations of its component, in the order of the
-//      rounds R1..R5 of interaction_accel_dpp.
-// Row h of 16 lanes holds four planets; an eight-planet group takes two rows.
-// Lane c of planet (h, r) evaluates the pair with
-//   c = 0: (h, r + 1)   R1            c = 1: (h, r + 2)   R2
-//   c = 2: (h', r + 1)  R3            c = 3: (h', r) R4 if h = 0, (h', r + 2) R5 if h = 1
-// (r modulo 4, h' the other row).  Positions and 1/r^3 are stored twice along
-// r, so that "r + k modulo 4" is a constant offset.
+//   3. it adds the pairs' accelerations of its component, in the layout's order.
 #pragma once
 #include "wh_step.h"
 
@@ -40,6 +35,7 @@ constexpr int WIDE_LDS = 256;    // doubles of LDS per wavefront
 
 constexpr int DPP_QUAD_0 = 0x00, DPP_QUAD_1 = 0x55, DPP_QUAD_2 = 0xAA;   // quad_perm: all lanes read lane 0, 1, 2
 constexpr int DPP_QUAD_REV = 0x1B;                                       // quad_perm [3,2,1,0]
+constexpr int DPP_ROW_MIRROR = 0x140;                                    // lane l of a row reads lane 15 - l
 
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -54,24 +50,36 @@ __device__ __forceinline__ void row_pair(int v, int& even, int& odd) {
   odd = (int)s[1];
 }
 
-// group_sum over the planets of a group, of the lane's component: the same
-// butterfly, planet p ^ 1 four lanes away (half-row mirror, then each quad
-// reversed), p ^ 2 eight, and the other four planets in the other row.
-template <int G> __device__ __forceinline__ double wide_sum(double v) {
+// Planet p ^ 1's lane of the same component (half-row mirror, then each quad
+// reversed), and planet 3 - r's of the row (row mirror, then reversed).
+__device__ __forceinline__ double wide_xor1(double v) { return dpp<DPP_QUAD_REV>(dpp<DPP_HALF_MIRROR>(v)); }
+__device__ __forceinline__ double wide_flip(double v) { return dpp<DPP_QUAD_REV>(dpp<DPP_ROW_MIRROR>(v)); }
+
+// group_momentum of the lane's component: sum over the group's planets of
+// m v.  The butterfly's first stage adds the neighbour's rounded product to
+// the lane's own by an FMA, so the sums of two neighbours may differ in the
+// last bit, and every later stage has to read the planet it reads there: in
+// the one-planet groups p ^ 2, then 7 - p; in the split layout 3 - p of the
+// half-row, then p ^ 4.
+template <int G, int STORAGE> __device__ __forceinline__ double wide_momentum(double m, double v) {
 #pragma clang fp contract(off)
-  if (G >= 2) v += dpp<DPP_QUAD_REV>(dpp<DPP_HALF_MIRROR>(v));
-  if (G >= 4) v += dpp<DPP_ROR8>(v);
-  if (G >= 8) {
-    int l0, l1, h0, h1;
-    row_pair(__double2loint(v), l0, l1);
-    row_pair(__double2hiint(v), h0, h1);
-    v = __hiloint2double(h0, l0) + __hiloint2double(h1, l1);
+  if (G == 1) return m * v;
+  double t = fma(m, v, wide_xor1(m * v));
+  if (G == 2) return t;
+  if (STORAGE == 1) t += wide_flip(t);
+  else t += dpp<DPP_ROR8>(t);
+  if (G == 4) return t;
+  int l0, l1, h0, h1;
+  if (STORAGE == 1) {
+    row_pair(__double2loint(t), l0, l1);
+    row_pair(__double2hiint(t), h0, h1);
+    return __hiloint2double(h0, l0) + __hiloint2double(h1, l1);
   }
-  return v;
-}
-template <int G> __device__ __forceinline__ double wide_momentum(double m, double v) {
-#pragma clang fp contract(off)
-  return wide_sum<G>(m * v);
+  const double u = wide_flip(t);
+  row_pair(__double2loint(u), l0, l1);
+  row_pair(__double2hiint(u), h0, h1);
+  const bool odd = threadIdx.x & 16;
+  return t + __hiloint2double(odd ? h0 : h1, odd ? l0 : l1);
 }
 template <int G> __device__ __forceinline__ int wide_or(int f) {
   if (G >= 2) f |= dpp_i<DPP_QUAD_REV>(dpp_i<DPP_HALF_MIRROR>(f));
@@ -84,9 +92,16 @@ template <int G> __device__ __forceinline__ int wide_or(int f) {
   return f;
 }
 
-// Where a lane reads and writes the wavefront's LDS block (positions at
-// [row][8][4], 1/r^3 at 128 + [row][pair c][8]), and the partners' masses.
-template <int G> struct WideKick {
+// The kick of the one-planet groups.  Row h of 16 lanes holds four planets;
+// an eight-planet group takes two rows.  Lane c of planet (h, r) evaluates the
+// pair with
+//   c = 0: (h, r + 1)   R1            c = 1: (h, r + 2)   R2
+//   c = 2: (h', r + 1)  R3            c = 3: (h', r) R4 if h = 0, (h', r + 2) R5 if h = 1
+// (r modulo 4, h' the other row; R1..R5 the rounds of interaction_accel_dpp,
+// in whose order step 3 adds).  Positions ([row][8][4]) and 1/r^3 (128 +
+// [row][c][8]) are stored twice along r, so that "r + k modulo 4" is a
+// constant offset.
+template <int G, int STORAGE> struct WideKick {
   double* lds;
   int iq, io, in, ip;            // own and other row's component, own planet, pair partner
   int iw, ie, ier3, ie4, ie5;    // 1/r^3: the lane's own, its planet's
@@ -162,6 +177,63 @@ template <int G> struct WideKick {
   }
 };
 
+// The split layout's kick: planet p of the ring of eight, lane c evaluates the
+// pair with p + c + 1.  Step 3 adds the pairs of the layout's copy 0, those of
+// copy 1, then the two (accel_split); pairs at distance 4 count once, with
+// zero masses on the side that repeats them.  Positions ([system][16][4]) and
+// 1/r^3 (128 + [system][c][16]) are stored twice along the ring.
+template <> struct WideKick<8, 1> {
+  double* lds;
+  int iq, in, ip, iw, ie;
+  double m1, m2, m3, m4, m1r, m2r, m3r, m4r;   // partners p + k, and p - k whose reaction comes back
+
+  __device__ __forceinline__ void init(double* block, int lane, double m) {
+    lds = block;
+    const int c = lane & 3, comp = c == 3 ? 0 : c, p = (lane >> 2) & 7, sys = lane >> 5;
+    in = sys * 64 + p * 4;
+    iq = in + comp;
+    ip = in + (c + 1) * 4;
+    ie = 128 + sys * 64 + p;
+    iw = ie + c * 16;
+    lds[iq] = m;
+    lds[iq + 32] = m;
+    wave_lds_fence();
+    m1 = lds[iq + 4]; m2 = lds[iq + 8]; m3 = lds[iq + 12];
+    m1r = lds[iq + 28]; m2r = lds[iq + 24]; m3r = lds[iq + 20];
+    const double mo = lds[iq + 16];
+    m4 = p >= 4 ? 0.0 : mo;
+    m4r = p >= 4 ? mo : 0.0;
+    wave_lds_fence();
+  }
+
+  __device__ __forceinline__ double accel(double q, double& x, double& y, double& z) const {
+#pragma clang fp contract(off)
+    lds[iq] = q;
+    lds[iq + 32] = q;
+    wave_lds_fence();
+    x = lds[in]; y = lds[in + 1]; z = lds[in + 2];
+    const double px = lds[ip], py = lds[ip + 1], pz = lds[ip + 2];
+    const double q1 = lds[iq + 4], q2 = lds[iq + 8], q3 = lds[iq + 12], q4 = lds[iq + 16];
+    const double q3r = lds[iq + 20], q2r = lds[iq + 24], q1r = lds[iq + 28];
+    const double dx = x - px, dy = y - py, dz = z - pz;
+    const double ir3 = rsqrt3_full(fma(dx, dx, fma(dy, dy, dz * dz)));
+    lds[iw] = ir3;
+    lds[iw + 8] = ir3;
+    wave_lds_fence();
+    const double e1 = lds[ie], e1r = lds[ie + 7], e2 = lds[ie + 16], e2r = lds[ie + 22];
+    const double e3 = lds[ie + 32], e3r = lds[ie + 37], e4 = lds[ie + 48], e4r = lds[ie + 52];
+    double a0 = fma(-(m1 * e1), q - q1, 0.0);
+    a0 += (m2r * e2r) * (q2r - q);
+    a0 = fma(-(m3 * e3), q - q3, a0);
+    a0 += (m4r * e4r) * (q4 - q);
+    double a1 = fma(-(m2 * e2), q - q2, 0.0);
+    a1 += (m1r * e1r) * (q1r - q);
+    a1 = fma(-(m4 * e4), q - q4, a1);
+    a1 += (m3r * e3r) * (q3r - q);
+    return a0 + a1;
+  }
+};
+
 // The lane's component of its planet's compensated state, and the planet's
 // constants.
 struct WideLane {
@@ -173,42 +245,49 @@ __device__ __forceinline__ int wide_comp(int lane) { return (lane & 3) == 3 ? 0 
 
 // Kepler drift (drift of wh_step.h): the whole planet's coefficients, the
 // lane's component of the map.  Returns the anomaly.
-template <int KC, class D>
-__device__ __forceinline__ double wide_drift(WideLane& L, double tau, D& dg) {
+template <int KC>
+__device__ __forceinline__ double wide_drift(WideLane& L, double tau, KepDiag& dg) {
   KepCoef k;
   const double X = kepler_coeffs<KepSet<KC>::NH, KepSet<KC>::NN, KepSet<KC>::KH, KepSet<KC>::KN>(
       dpp<DPP_QUAD_0>(L.q), dpp<DPP_QUAD_1>(L.q), dpp<DPP_QUAD_2>(L.q), dpp<DPP_QUAD_0>(L.v), dpp<DPP_QUAD_1>(L.v),
       dpp<DPP_QUAD_2>(L.v), L.m0, tau, dg, k);
-  const double q0 = L.q, cq0 = L.cq;
-  linear_dd(k.fm1, L.q, L.cq, k.g, L.v, L.cv);
-  linear_dd(k.gdm1, L.v, L.cv, k.fd, q0, cq0);
+  double hq, lq, hv, lv;
+  lin2_dd(k.fm1, L.q, k.g, L.v, hq, lq);
+  lin2_dd(k.gdm1, L.v, k.fd, L.q, hv, lv);
+  lq = fma(k.fm1, L.cq, fma(k.g, L.cv, lq));
+  lv = fma(k.fd, L.cq, fma(k.gdm1, L.cv, lv));
+  add_hi(L.q, L.cq, hq, lq);
+  add_hi(L.v, L.cv, hv, lv);
   return X;
 }
 
 // kick_block on the lane's component; vk: its velocity after the kick.
-template <int G, bool GR>
-__device__ __forceinline__ void wide_kick(WideLane& L, const WideKick<G>& wk, double inv_m0, double kg, double ta,
+template <int G, bool GR, int STORAGE>
+__device__ __forceinline__ void wide_kick(WideLane& L, const WideKick<G, STORAGE>& wk, double inv_m0, double kg, double ta,
                                           double ti, double tc, double& vk) {
   double q = L.q, x, y, z;
   if (GR) {
-    const double s = wide_momentum<G>(L.m, L.v), k1 = ta * inv_m0;
+    const double s = wide_momentum<G, STORAGE>(L.m, L.v), k1 = ta * inv_m0;
     L.cq = fma(k1, s, L.cq);
     q = fma(k1, s, q);
   }
   double a = wk.accel(q, x, y, z);
-  if (GR) a = fma(gr_weight(x, y, z, kg), q, a);
+  if (GR) {
+    const double ir2 = rcp_full(fma(x, x, fma(y, y, z * z)));   // gr_accel
+    a = fma(-kg * ir2 * ir2, q, a);
+  }
   L.cv = fma(ti, a, L.cv);
   vk = fma(ti, a, L.v);
-  const double s = wide_momentum<G>(L.m, vk);
+  const double s = wide_momentum<G, STORAGE>(L.m, vk);
   L.cq = fma((GR ? tc : ta + tc) * inv_m0, s, L.cq);
   renorm(L.q, L.cq);
   renorm(L.v, L.cv);
 }
 
 // step_lane for four lanes per planet (DHC).
-template <int G, bool GR, int SCHEME, int KC>
+template <int G, bool GR, int SCHEME, int KC, int STORAGE>
 __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, double* block, int lane) {
-  WideKick<G> wk;
+  WideKick<G, STORAGE> wk;
   wk.init(block, lane, L.m);
   const double dt = L.dt, h = 0.5 * dt;
   const double inv_m0 = 1.0 / L.m0;
@@ -226,7 +305,7 @@ __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, dou
       for (int k = 0; k < n_units; ++k) {
         wide_drift<0>(L, tk, dg);
         const double tb = (k == 0 ? sd0 : k == 1 ? sd1 : k == 2 ? sd2 : sd3) * dt;
-        wide_kick<G, false>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
+        wide_kick<G, false, STORAGE>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
         tk = k + 1 < n_units ? (k == 0 ? sc1 : k == 1 ? sc2 : sc3) * dt : 2.0 * c1dt;
       }
     }
@@ -235,13 +314,13 @@ __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, dou
     for (int s = 0; s < n_steps; ++s) {
       wide_drift<KC>(L, tk, dg);
       tk = dt;
-      wide_kick<G, GR>(L, wk, inv_m0, kg, h, dt, h, vk);
+      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, h, dt, h, vk);
     }
   } else {
     double ta = L.first ? 0.0 : h;
     double ti = L.first ? h : dt;
     for (int s = 0; s < n_steps; ++s) {
-      wide_kick<G, GR>(L, wk, inv_m0, kg, ta, ti, h, vk);
+      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, ta, ti, h, vk);
       ta = h;
       ti = dt;
       wide_drift<KC>(L, dt, dg);
@@ -286,7 +365,7 @@ __device__ __forceinline__ void wide_group(const StepParams& p, int w, double* b
   L.sys = p.slot_sys[slot];
   L.pl = p.slot_pl[slot];
   L.first = L.sys >= 0 ? p.synced[L.sys] : 1;
-  wide_steps<G, GR, SCHEME, KC>(p, L, block, lane);
+  wide_steps<G, GR, SCHEME, KC, STORAGE>(p, L, block, lane);
   if ((lane & 3) < 3) {
     st[0] = L.q;
     st[r3] = L.v;
@@ -327,9 +406,9 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
   const double inv_m0 = 1.0 / L.m0;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
   const bool comp = (lane & 3) < 3;
-  WideKick<G> wk;
+  WideKick<G, STORAGE> wk;
   wk.init(block, lane, L.m);
-  KepNoDiag dg;
+  KepDiag dg{0.0, 1.0e300};   // not read
   double vk;
   double* row = tape + (size_t)c * ns + slot;         // the lane's rows: c, 3 + c, 7 + c
   double* xrow = tape + (size_t)6 * ns + slot;
@@ -351,7 +430,7 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
         const double tb = p.sd[k] * dt;
         put_state();
         const double X = wide_drift<0>(L, tau, dg);
-        wide_kick<G, false>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
+        wide_kick<G, false, STORAGE>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
         put_rest(X);
       }
   } else if constexpr (SCHEME == WH_KDK) {
@@ -359,7 +438,7 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
     double ti = first_synced ? h : dt;
     for (int s = 0; s < n_rec; ++s) {
       put_state();
-      wide_kick<G, GR>(L, wk, inv_m0, kg, ta, ti, h, vk);
+      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, ta, ti, h, vk);
       ta = h;
       ti = dt;
       put_rest(wide_drift<0>(L, dt, dg));
@@ -370,7 +449,7 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
       put_state();
       const double X = wide_drift<0>(L, tk, dg);
       tk = dt;
-      wide_kick<G, GR>(L, wk, inv_m0, kg, h, dt, h, vk);
+      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, h, dt, h, vk);
       put_rest(X);
     }
   }
