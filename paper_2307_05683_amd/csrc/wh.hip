@@ -651,6 +651,33 @@ __device__ __forceinline__ void serial_kick_drift(SerialState<NP>& S, double* cl
   }
 }
 
+// The end of a launch: state and compensation to memory, the system's flags.
+template <int NP>
+__device__ __forceinline__ void serial_end(const StepParams& p, const SerialState<NP>& S, double* cl, int base, int n,
+                                           const KepDiag& dg) {
+  const int ns = p.ns, sys = p.slot_sys[base];
+  int f = 0;
+  double* so = p.st;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const bool fin = __builtin_isfinite(S.qx[i]) && __builtin_isfinite(S.qy[i]) && __builtin_isfinite(S.qz[i]) &&
+                     __builtin_isfinite(S.vx[i]) && __builtin_isfinite(S.vy[i]) && __builtin_isfinite(S.vz[i]);
+    if (i < n && !fin) f |= WH_F_NONFINITE;
+    so[base + i] = S.qx[i];
+    so[ns + base + i] = S.qy[i];
+    so[2 * ns + base + i] = S.qz[i];
+    so[3 * ns + base + i] = S.vx[i];
+    so[4 * ns + base + i] = S.vy[i];
+    so[5 * ns + base + i] = S.vz[i];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) so[(7 + k) * ns + base + i] = comp_at(cl, k, i);
+  }
+  if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
+  if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
+  p.flags[sys] |= (uint32_t)f;
+  p.synced[sys] = 0;
+}
+
 template <int NP, bool GR, int SCHEME>
 __device__ void step_serial(const StepParams& p, int base, int n, double* cl) {
   const double* st = p.st;
@@ -717,26 +744,7 @@ __device__ void step_serial(const StepParams& p, int base, int n, double* cl) {
       ti = dt;
     }
   }
-  int f = 0;
-  double* so = p.st;
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const bool fin = __builtin_isfinite(S.qx[i]) && __builtin_isfinite(S.qy[i]) && __builtin_isfinite(S.qz[i]) &&
-                     __builtin_isfinite(S.vx[i]) && __builtin_isfinite(S.vy[i]) && __builtin_isfinite(S.vz[i]);
-    if (i < n && !fin) f |= WH_F_NONFINITE;
-    so[base + i] = S.qx[i];
-    so[ns + base + i] = S.qy[i];
-    so[2 * ns + base + i] = S.qz[i];
-    so[3 * ns + base + i] = S.vx[i];
-    so[4 * ns + base + i] = S.vy[i];
-    so[5 * ns + base + i] = S.vz[i];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) so[(7 + k) * ns + base + i] = comp_at(cl, k, i);
-  }
-  if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
-  if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
-  p.flags[sys] |= (uint32_t)f;
-  p.synced[sys] = 0;
+  serial_end<NP>(p, S, cl, base, n, dg);
 }
 
 // Dynamic LDS: SERIAL_LDS_PER_WAVE doubles per wave of the block.
@@ -1334,7 +1342,23 @@ __device__ __forceinline__ void kick_block_vjp(Grad& a, const Exch<G, 1>& ex, do
 // state at the start of the step, the anomaly X of its drift and the
 // velocity after its kick; with KDK the step is the kick block followed by
 // the drift.
-template <int G, bool GR, int SCH = WH_DKD>
+//
+// FIN: the segment is the run's last one, recorded as the forward run takes
+// it: its end is stored as the context's state, with the flags (what the step
+// kernel's end does), so that the reverse pass need not run it again.
+template <int G>
+__device__ __forceinline__ void record_end(const StepParams& p, Lane& L, const KepDiag& dg, int slot, int lane) {
+  L.sys = p.slot_sys[slot];
+  L.pl = p.slot_pl[slot];
+  const int f = group_or<G>(lane_flags(L, dg, p.zlim));
+  if ((lane & (G - 1)) == 0 && L.sys >= 0) {
+    p.flags[L.sys] |= (uint32_t)f;
+    p.synced[L.sys] = 0;
+  }
+  store_lane(p, slot, L);
+}
+
+template <int G, bool GR, int SCH = WH_DKD, bool FIN = false>
 __device__ void adj_record_lane(const AdjParams& q, int slot, int lane) {
   const StepParams& p = q.sp;
   const int ns = p.ns;
@@ -1366,9 +1390,7 @@ __device__ void adj_record_lane(const AdjParams& q, int slot, int lane) {
         kick_block<G, false, 1>(L, ex, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vkx, vky, vkz);
         row[7 * ns] = vkx; row[8 * ns] = vky; row[9 * ns] = vkz;
       }
-    return;
-  }
-  if constexpr (SCH == WH_KDK) {
+  } else if constexpr (SCH == WH_KDK) {
     double ta = q.rec_first_synced ? 0.0 : h;
     double ti = q.rec_first_synced ? h : dt;
     for (int s = 0; s < q.n_rec; ++s) {
@@ -1382,19 +1404,20 @@ __device__ void adj_record_lane(const AdjParams& q, int slot, int lane) {
       ti = dt;
       row[6 * ns] = drift(L, L.m0, dt, dg);
     }
-    return;
+  } else {
+    double tk = q.rec_first_synced ? h : dt;
+    for (int s = 0; s < q.n_rec; ++s) {
+      double* row = q.tape_rec + (size_t)s * TAPE_ROWS * ns + slot;
+      row[0] = L.qx; row[ns] = L.qy; row[2 * ns] = L.qz;
+      row[3 * ns] = L.vx; row[4 * ns] = L.vy; row[5 * ns] = L.vz;
+      row[6 * ns] = drift(L, L.m0, tk, dg);
+      tk = dt;
+      double vkx, vky, vkz;
+      kick_block<G, GR, 1>(L, ex, inv_m0, kg, h, dt, h, vkx, vky, vkz);
+      row[7 * ns] = vkx; row[8 * ns] = vky; row[9 * ns] = vkz;   // V after the kick
+    }
   }
-  double tk = q.rec_first_synced ? h : dt;
-  for (int s = 0; s < q.n_rec; ++s) {
-    double* row = q.tape_rec + (size_t)s * TAPE_ROWS * ns + slot;
-    row[0] = L.qx; row[ns] = L.qy; row[2 * ns] = L.qz;
-    row[3 * ns] = L.vx; row[4 * ns] = L.vy; row[5 * ns] = L.vz;
-    row[6 * ns] = drift(L, L.m0, tk, dg);
-    tk = dt;
-    double vkx, vky, vkz;
-    kick_block<G, GR, 1>(L, ex, inv_m0, kg, h, dt, h, vkx, vky, vkz);
-    row[7 * ns] = vkx; row[8 * ns] = vky; row[9 * ns] = vkz;   // V after the kick
-  }
+  if (FIN) record_end<G>(p, L, dg, slot, lane);
 }
 
 // One step's row of a segment tape (TAPE_ROWS values of one slot).
@@ -1565,8 +1588,8 @@ __device__ __forceinline__ void kick_block_vjp_pair(Grad& a, Grad& b, const Pair
 
 // The same two roles in the pair layout: lane l of wave w holds slots
 // 128 w + l (a) and 128 w + 64 + l (b).
-template <int G, bool GR, int SCH = WH_DKD>
-__device__ void adj_record_pair(const AdjParams& q, int sa) {
+template <int G, bool GR, int SCH = WH_DKD, bool FIN = false>
+__device__ void adj_record_pair(const AdjParams& q, int sa, int lane) {
   const StepParams& p = q.sp;
   const int ns = p.ns, sb = sa + 64;
   Lane A, B;
@@ -1597,9 +1620,7 @@ __device__ void adj_record_pair(const AdjParams& q, int sa) {
         ra[7 * ns] = vka[0]; ra[8 * ns] = vka[1]; ra[9 * ns] = vka[2];
         rb[7 * ns] = vkb[0]; rb[8 * ns] = vkb[1]; rb[9 * ns] = vkb[2];
       }
-    return;
-  }
-  if constexpr (SCH == WH_KDK) {
+  } else if constexpr (SCH == WH_KDK) {
     double ta = q.rec_first_synced ? 0.0 : h;
     double ti = q.rec_first_synced ? h : dt;
     for (int s = 0; s < q.n_rec; ++s) {
@@ -1616,21 +1637,33 @@ __device__ void adj_record_pair(const AdjParams& q, int sa) {
       ra[6 * ns] = drift(A, A.m0, dt, dga);
       rb[6 * ns] = drift(B, B.m0, dt, dgb);
     }
-    return;
+  } else {
+    double tk = q.rec_first_synced ? h : dt;
+    for (int s = 0; s < q.n_rec; ++s) {
+      double* ra = q.tape_rec + (size_t)s * TAPE_ROWS * ns + sa;
+      double* rb = ra + 64;
+      ra[0] = A.qx; ra[ns] = A.qy; ra[2 * ns] = A.qz; ra[3 * ns] = A.vx; ra[4 * ns] = A.vy; ra[5 * ns] = A.vz;
+      rb[0] = B.qx; rb[ns] = B.qy; rb[2 * ns] = B.qz; rb[3 * ns] = B.vx; rb[4 * ns] = B.vy; rb[5 * ns] = B.vz;
+      ra[6 * ns] = drift(A, A.m0, tk, dga);
+      rb[6 * ns] = drift(B, B.m0, tk, dgb);
+      tk = dt;
+      double vka[3], vkb[3];
+      kick_block_pair<G, GR>(A, B, pm, inv_m0, kg, h, dt, h, vka, vkb);
+      ra[7 * ns] = vka[0]; ra[8 * ns] = vka[1]; ra[9 * ns] = vka[2];
+      rb[7 * ns] = vkb[0]; rb[8 * ns] = vkb[1]; rb[9 * ns] = vkb[2];
+    }
   }
-  double tk = q.rec_first_synced ? h : dt;
-  for (int s = 0; s < q.n_rec; ++s) {
-    double* ra = q.tape_rec + (size_t)s * TAPE_ROWS * ns + sa;
-    double* rb = ra + 64;
-    ra[0] = A.qx; ra[ns] = A.qy; ra[2 * ns] = A.qz; ra[3 * ns] = A.vx; ra[4 * ns] = A.vy; ra[5 * ns] = A.vz;
-    rb[0] = B.qx; rb[ns] = B.qy; rb[2 * ns] = B.qz; rb[3 * ns] = B.vx; rb[4 * ns] = B.vy; rb[5 * ns] = B.vz;
-    ra[6 * ns] = drift(A, A.m0, tk, dga);
-    rb[6 * ns] = drift(B, B.m0, tk, dgb);
-    tk = dt;
-    double vka[3], vkb[3];
-    kick_block_pair<G, GR>(A, B, pm, inv_m0, kg, h, dt, h, vka, vkb);
-    ra[7 * ns] = vka[0]; ra[8 * ns] = vka[1]; ra[9 * ns] = vka[2];
-    rb[7 * ns] = vkb[0]; rb[8 * ns] = vkb[1]; rb[9 * ns] = vkb[2];
+  if (FIN) {
+    A.sys = B.sys = p.slot_sys[sa];
+    A.pl = p.slot_pl[sa];
+    B.pl = p.slot_pl[sb];
+    const int f = group_or<G>(lane_flags(A, dga, p.zlim) | lane_flags(B, dgb, p.zlim));
+    if ((lane & (G - 1)) == 0 && A.sys >= 0) {
+      p.flags[A.sys] |= (uint32_t)f;
+      p.synced[A.sys] = 0;
+    }
+    store_lane(p, sa, A);
+    store_lane(p, sb, B);
   }
 }
 
@@ -1775,11 +1808,11 @@ __device__ void adj_sweep_pair(const AdjParams& q, int sa, int lane) {
   store_grad(q.grad, ns, sb, b);
 }
 
-template <bool GR, int SCH> __global__ __launch_bounds__(256) void k_adj_segment_pair(AdjParams q) {
+template <bool GR, int SCH, bool FIN> __global__ __launch_bounds__(256) void k_adj_segment_pair(AdjParams q) {
   const StepParams& p = q.sp;
   const int lane = threadIdx.x & 63;
   int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const bool sweep = wave < q.sweep_waves;
+  const bool sweep = !FIN && wave < q.sweep_waves;
   if (!sweep) wave -= q.sweep_waves;
   if (wave >= p.w8) return;
   const int sa = wave * 128 + lane;
@@ -1788,9 +1821,9 @@ template <bool GR, int SCH> __global__ __launch_bounds__(256) void k_adj_segment
     else if (wave < p.w2) adj_sweep_pair<2, GR, SCH>(q, sa, lane);
     else adj_sweep_pair<4, GR, SCH>(q, sa, lane);
   } else {
-    if (wave < p.w1) adj_record_pair<1, GR, SCH>(q, sa);
-    else if (wave < p.w2) adj_record_pair<2, GR, SCH>(q, sa);
-    else adj_record_pair<4, GR, SCH>(q, sa);
+    if (wave < p.w1) adj_record_pair<1, GR, SCH, FIN>(q, sa, lane);
+    else if (wave < p.w2) adj_record_pair<2, GR, SCH, FIN>(q, sa, lane);
+    else adj_record_pair<4, GR, SCH, FIN>(q, sa, lane);
   }
 }
 
@@ -1798,38 +1831,38 @@ template <bool GR, int SCH> __global__ __launch_bounds__(256) void k_adj_segment
 // previous segment; each role covers the packing's waves once.  Contexts whose
 // step runs with four lanes per planet record in that form too (the same bits
 // as the step, which recording repeats).
-template <bool GR, bool SPLIT, int SCH> __global__ __launch_bounds__(64) void k_adj_segment(AdjParams q) {
+template <bool GR, bool SPLIT, int SCH, bool FIN> __global__ __launch_bounds__(64) void k_adj_segment(AdjParams q) {
   __shared__ double lds[WIDE_LDS];
   const StepParams& p = q.sp;
   const int lane = threadIdx.x;
   int wave = (int)blockIdx.x;
-  const bool sweep = wave < q.sweep_waves;
+  const bool sweep = !FIN && wave < q.sweep_waves;
   if (!sweep) wave -= q.sweep_waves;
   if (!sweep && q.wide_record > 0) {
     if (wave >= q.wide_record) return;
     const bool first = q.rec_first_synced != 0;
-    if (SPLIT) wide_record<8, GR, SCH, 1>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else if (wave < 4 * p.w1) wide_record<1, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else if (wave < 4 * p.w2) wide_record<2, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else if (wave < 4 * p.w4) wide_record<4, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else wide_record<8, GR, SCH, 0>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    if (SPLIT) wide_record<8, GR, SCH, 1, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else if (wave < 4 * p.w1) wide_record<1, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else if (wave < 4 * p.w2) wide_record<2, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else if (wave < 4 * p.w4) wide_record<4, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+    else wide_record<8, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
     return;
   }
   if (wave >= p.w8) return;
   const int slot = wave * 64 + lane;
   if (SPLIT) {
     if (sweep) adj_sweep_lane<G_SPLIT, GR, SCH>(q, slot, lane);
-    else adj_record_lane<G_SPLIT, GR, SCH>(q, slot, lane);
+    else adj_record_lane<G_SPLIT, GR, SCH, FIN>(q, slot, lane);
   } else if (sweep) {
     if (wave < p.w1) adj_sweep_lane<1, GR, SCH>(q, slot, lane);
     else if (wave < p.w2) adj_sweep_lane<2, GR, SCH>(q, slot, lane);
     else if (wave < p.w4) adj_sweep_lane<4, GR, SCH>(q, slot, lane);
     else adj_sweep_lane<8, GR, SCH>(q, slot, lane);
   } else {
-    if (wave < p.w1) adj_record_lane<1, GR, SCH>(q, slot, lane);
-    else if (wave < p.w2) adj_record_lane<2, GR, SCH>(q, slot, lane);
-    else if (wave < p.w4) adj_record_lane<4, GR, SCH>(q, slot, lane);
-    else adj_record_lane<8, GR, SCH>(q, slot, lane);
+    if (wave < p.w1) adj_record_lane<1, GR, SCH, FIN>(q, slot, lane);
+    else if (wave < p.w2) adj_record_lane<2, GR, SCH, FIN>(q, slot, lane);
+    else if (wave < p.w4) adj_record_lane<4, GR, SCH, FIN>(q, slot, lane);
+    else adj_record_lane<8, GR, SCH, FIN>(q, slot, lane);
   }
 }
 
@@ -1856,7 +1889,7 @@ __device__ __forceinline__ void record_static(const AdjParams& q, int base, int 
   }
 }
 
-template <int NP, bool GR, int SCH>
+template <int NP, bool GR, int SCH, bool FIN>
 __device__ void adj_record_serial(const AdjParams& q, int base, int n, double* cl) {
   const StepParams& p = q.sp;
   const int ns = p.ns;
@@ -1895,10 +1928,7 @@ __device__ void adj_record_serial(const AdjParams& q, int base, int n, double* c
         serial_kick_drift<NP, false, true>(S, cl, n, m0, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, 0.0, false, dg,
                                            row + 7 * ns, ns);
       }
-    record_static(q, base, NP);
-    return;
-  }
-  if constexpr (SCH == WH_KDK) {
+  } else if constexpr (SCH == WH_KDK) {
     double ta = q.rec_first_synced ? 0.0 : h;
     double ti = q.rec_first_synced ? h : dt;
     for (int s = 0; s < q.n_rec; ++s) {
@@ -1913,40 +1943,40 @@ __device__ void adj_record_serial(const AdjParams& q, int base, int n, double* c
       ta = h;
       ti = dt;
     }
-    record_static(q, base, NP);
-    return;
-  }
-  double tk = q.rec_first_synced ? h : dt;
-  for (int s = 0; s < q.n_rec; ++s) {
-    double* row = q.tape_rec + (size_t)s * TAPE_ROWS * ns + base;
+  } else {
+    double tk = q.rec_first_synced ? h : dt;
+    for (int s = 0; s < q.n_rec; ++s) {
+      double* row = q.tape_rec + (size_t)s * TAPE_ROWS * ns + base;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      row[i] = S.qx[i]; row[ns + i] = S.qy[i]; row[2 * ns + i] = S.qz[i];
-      row[3 * ns + i] = S.vx[i]; row[4 * ns + i] = S.vy[i]; row[5 * ns + i] = S.vz[i];
-      Lane L = serial_get(S, cl, i);
-      row[6 * ns + i] = serial_drift(L, m0, tk, i < n, dg);
-      serial_put(S, cl, i, L);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < NP; ++i) {
+        row[i] = S.qx[i]; row[ns + i] = S.qy[i]; row[2 * ns + i] = S.qz[i];
+        row[3 * ns + i] = S.vx[i]; row[4 * ns + i] = S.vy[i]; row[5 * ns + i] = S.vz[i];
+        Lane L = serial_get(S, cl, i);
+        row[6 * ns + i] = serial_drift(L, m0, tk, i < n, dg);
+        serial_put(S, cl, i, L);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      tk = dt;
+      serial_kick_drift<NP, GR, true>(S, cl, n, m0, inv_m0, kg, h, dt, h, 0.0, false, dg, row + 7 * ns, ns);
     }
-    tk = dt;
-    serial_kick_drift<NP, GR, true>(S, cl, n, m0, inv_m0, kg, h, dt, h, 0.0, false, dg, row + 7 * ns, ns);
   }
   record_static(q, base, NP);
+  if (FIN) serial_end<NP>(p, S, cl, base, n, dg);
 }
 
 // Waves [0, sweep_waves) sweep (G8 waves, one planet per lane); the others
 // record, one thread per 8-slot group, with SERIAL_LDS_PER_WAVE doubles of
 // dynamic LDS per wave (one-wave workgroups).
-template <bool GR, int SCH> __global__ __launch_bounds__(64) void k_adj_segment_serial(AdjParams q) {
+template <bool GR, int SCH, bool FIN> __global__ __launch_bounds__(64) void k_adj_segment_serial(AdjParams q) {
   extern __shared__ double serial_lds[];
   const StepParams& p = q.sp;
   const int lane = threadIdx.x;
   const int wave = blockIdx.x;
-  if (wave < q.sweep_waves) {
+  if (!FIN && wave < q.sweep_waves) {
     if (wave < p.w8) adj_sweep_lane<8, GR, SCH>(q, wave * 64 + lane, lane);
     return;
   }
-  const int g = (wave - q.sweep_waves) * 64 + lane;
+  const int g = (wave - (FIN ? 0 : q.sweep_waves)) * 64 + lane;
   if (g >= p.w8 * 8) return;
   const int base = g * 8;
   if (p.slot_sys[base] < 0) {
@@ -1962,14 +1992,14 @@ template <bool GR, int SCH> __global__ __launch_bounds__(64) void k_adj_segment_
   for (int k = 2; k <= 8; ++k)
     if (__ballot(n >= k) != 0) nw = k;
   switch (nw) {
-    case 1: adj_record_serial<1, GR, SCH>(q, base, n, cl); break;
-    case 2: adj_record_serial<2, GR, SCH>(q, base, n, cl); break;
-    case 3: adj_record_serial<3, GR, SCH>(q, base, n, cl); break;
-    case 4: adj_record_serial<4, GR, SCH>(q, base, n, cl); break;
-    case 5: adj_record_serial<5, GR, SCH>(q, base, n, cl); break;
-    case 6: adj_record_serial<6, GR, SCH>(q, base, n, cl); break;
-    case 7: adj_record_serial<7, GR, SCH>(q, base, n, cl); break;
-    default: adj_record_serial<8, GR, SCH>(q, base, n, cl); break;
+    case 1: adj_record_serial<1, GR, SCH, FIN>(q, base, n, cl); break;
+    case 2: adj_record_serial<2, GR, SCH, FIN>(q, base, n, cl); break;
+    case 3: adj_record_serial<3, GR, SCH, FIN>(q, base, n, cl); break;
+    case 4: adj_record_serial<4, GR, SCH, FIN>(q, base, n, cl); break;
+    case 5: adj_record_serial<5, GR, SCH, FIN>(q, base, n, cl); break;
+    case 6: adj_record_serial<6, GR, SCH, FIN>(q, base, n, cl); break;
+    case 7: adj_record_serial<7, GR, SCH, FIN>(q, base, n, cl); break;
+    default: adj_record_serial<8, GR, SCH, FIN>(q, base, n, cl); break;
   }
 }
 
@@ -2148,7 +2178,7 @@ __device__ __forceinline__ void dhc_to_jac_vjp(Grad& a, double& gMim1, const Jac
 // Recording and sweeping of a Jacobi context (per lane; tape rows as in DHC:
 // the state at the start of the step or unit, the drift's X, V' after the
 // kick).
-template <int G, bool GR, int SCH>
+template <int G, bool GR, int SCH, bool FIN>
 __device__ void adj_record_jac(const AdjParams& q, int slot, int lane) {
   const StepParams& p = q.sp;
   const int ns = p.ns;
@@ -2201,6 +2231,7 @@ __device__ void adj_record_jac(const AdjParams& q, int slot, int lane) {
       row[7 * ns] = vkx; row[8 * ns] = vky; row[9 * ns] = vkz;
     }
   }
+  if (FIN) record_end<G>(p, L, dg, slot, lane);
 }
 
 template <int G, bool GR, int SCH>
@@ -2269,11 +2300,11 @@ __device__ void adj_sweep_jac(const AdjParams& q, int slot, int lane) {
   store_grad(q.grad, ns, slot, a);
 }
 
-template <bool GR, int SCH> __global__ __launch_bounds__(256) void k_adj_segment_jac(AdjParams q) {
+template <bool GR, int SCH, bool FIN> __global__ __launch_bounds__(256) void k_adj_segment_jac(AdjParams q) {
   const StepParams& p = q.sp;
   const int lane = threadIdx.x & 63;
   int wave = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const bool sweep = wave < q.sweep_waves;
+  const bool sweep = !FIN && wave < q.sweep_waves;
   if (!sweep) wave -= q.sweep_waves;
   if (wave >= p.w8) return;
   const int slot = wave * 64 + lane;
@@ -2283,10 +2314,10 @@ template <bool GR, int SCH> __global__ __launch_bounds__(256) void k_adj_segment
     else if (wave < p.w4) adj_sweep_jac<4, GR, SCH>(q, slot, lane);
     else adj_sweep_jac<8, GR, SCH>(q, slot, lane);
   } else {
-    if (wave < p.w1) adj_record_jac<1, GR, SCH>(q, slot, lane);
-    else if (wave < p.w2) adj_record_jac<2, GR, SCH>(q, slot, lane);
-    else if (wave < p.w4) adj_record_jac<4, GR, SCH>(q, slot, lane);
-    else adj_record_jac<8, GR, SCH>(q, slot, lane);
+    if (wave < p.w1) adj_record_jac<1, GR, SCH, FIN>(q, slot, lane);
+    else if (wave < p.w2) adj_record_jac<2, GR, SCH, FIN>(q, slot, lane);
+    else if (wave < p.w4) adj_record_jac<4, GR, SCH, FIN>(q, slot, lane);
+    else adj_record_jac<8, GR, SCH, FIN>(q, slot, lane);
   }
 }
 
@@ -2793,6 +2824,7 @@ struct wh_ctx {
   const void* tape = nullptr;
   size_t tape_bytes = 0;
   int64_t tape_steps = 0, tape_every = 0, tape_end = -1;
+  bool tape_last = false;   // its segment tape still holds the last segment
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -3128,19 +3160,58 @@ int tape_units(const wh_ctx* c) { return c->cfg.scheme >= WH_SABA2 ? c->cfg.sche
 // One launch of the reverse pass: sweep_waves wavefronts sweep a segment and
 // the following ones record the previous segment (record_waves wavefronts of
 // the packing; the serial packing records with one thread per 8-slot group).
-template <bool GR, int SCH>
+// FIN: the forward run's last segment, recorded and stored as its end.
+template <bool GR, int SCH, bool FIN>
 void launch_adj_segment(const wh_ctx* c, const AdjParams& q, int sweep_waves, int record_waves, hipStream_t st) {
   if (c->P.serial) {
     const int rec = record_waves > 0 ? (record_waves * 8 + 63) / 64 : 0;
     const dim3 grid(sweep_waves + rec), block(64);
     const size_t smem = SERIAL_LDS_PER_WAVE * sizeof(double);
-    hipLaunchKernelGGL((k_adj_segment_serial<GR, SCH>), grid, block, smem, st, q);
+    hipLaunchKernelGGL((k_adj_segment_serial<GR, SCH, FIN>), grid, block, smem, st, q);
     return;
   }
   const dim3 grid(sweep_waves + (record_waves > 0 && c->wide_waves > 0 ? c->wide_waves : record_waves)), block(64);
-  if (c->P.pair) hipLaunchKernelGGL((k_adj_segment_pair<GR, SCH>), grid, block, 0, st, q);
-  else if (c->P.split) hipLaunchKernelGGL((k_adj_segment<GR, true, SCH>), grid, block, 0, st, q);
-  else hipLaunchKernelGGL((k_adj_segment<GR, false, SCH>), grid, block, 0, st, q);
+  if (c->P.pair) hipLaunchKernelGGL((k_adj_segment_pair<GR, SCH, FIN>), grid, block, 0, st, q);
+  else if (c->P.split) hipLaunchKernelGGL((k_adj_segment<GR, true, SCH, FIN>), grid, block, 0, st, q);
+  else hipLaunchKernelGGL((k_adj_segment<GR, false, SCH, FIN>), grid, block, 0, st, q);
+}
+template <bool FIN>
+void launch_adj(const wh_ctx* c, AdjParams& q, int sweep_waves, int record_waves, hipStream_t st) {
+  q.sweep_waves = sweep_waves;
+  const bool gr = c->cfg.gr_c > 0, kdk = c->cfg.scheme == WH_KDK, saba = c->cfg.scheme >= WH_SABA2;
+  if (c->cfg.coords == WH_COORDS_JACOBI) {
+    const dim3 grid(sweep_waves + record_waves), block(64);
+    if (saba && gr) hipLaunchKernelGGL((k_adj_segment_jac<true, SCHEME_SABA, FIN>), grid, block, 0, st, q);
+    else if (saba) hipLaunchKernelGGL((k_adj_segment_jac<false, SCHEME_SABA, FIN>), grid, block, 0, st, q);
+    else if (kdk && gr) hipLaunchKernelGGL((k_adj_segment_jac<true, WH_KDK, FIN>), grid, block, 0, st, q);
+    else if (kdk) hipLaunchKernelGGL((k_adj_segment_jac<false, WH_KDK, FIN>), grid, block, 0, st, q);
+    else if (gr) hipLaunchKernelGGL((k_adj_segment_jac<true, WH_DKD, FIN>), grid, block, 0, st, q);
+    else hipLaunchKernelGGL((k_adj_segment_jac<false, WH_DKD, FIN>), grid, block, 0, st, q);
+    return;
+  }
+  if (saba) launch_adj_segment<false, SCHEME_SABA, FIN>(c, q, sweep_waves, record_waves, st);
+  else if (kdk && gr) launch_adj_segment<true, WH_KDK, FIN>(c, q, sweep_waves, record_waves, st);
+  else if (kdk) launch_adj_segment<false, WH_KDK, FIN>(c, q, sweep_waves, record_waves, st);
+  else if (gr) launch_adj_segment<true, WH_DKD, FIN>(c, q, sweep_waves, record_waves, st);
+  else launch_adj_segment<false, WH_DKD, FIN>(c, q, sweep_waves, record_waves, st);
+}
+
+// The parameters of a context's reverse pass that do not change from launch
+// to launch, and the choice of the segment to record (segment k goes into
+// segment tape k mod 2).
+AdjParams adj_params(const wh_ctx* c) {
+  AdjParams q;
+  memset(&q, 0, sizeof(q));
+  q.sp = step_params(c, 0);
+  q.wide_record = c->wide_waves;
+  return q;
+}
+int64_t segment_steps(int64_t n_steps, int64_t every, int64_t k) { return std::min<int64_t>(every, n_steps - k * every); }
+void set_record(AdjParams& q, char* tape, const TapeLayout& T, int ns, int64_t n_steps, int64_t every, int64_t k) {
+  q.ck_rec = (const double*)(tape + T.ck) + (size_t)k * 12 * ns;
+  q.tape_rec = (double*)(tape + T.seg[k & 1]);
+  q.n_rec = (int)segment_steps(n_steps, every, k);
+  q.rec_first_synced = (k == 0);
 }
 
 }  // namespace
@@ -3493,6 +3564,14 @@ wh_status wh_forward_ckpt(wh_ctx* c, int64_t n_steps, int64_t ckpt_every, void* 
   for (int64_t k = 0; k <= T.n_seg; ++k) {
     hipLaunchKernelGGL(k_save_ck, grd, blk, 0, stream, c->st, ck + (size_t)k * 12 * ns, ns);
     if (k == T.n_seg) break;
+    if (k == T.n_seg - 1) {
+      // the last segment is recorded on the way: the reverse pass starts by
+      // sweeping it
+      AdjParams q = adj_params(c);
+      set_record(q, (char*)tape, T, ns, n_steps, ckpt_every, k);
+      launch_adj<true>(c, q, 0, c->P.nwaves, stream);
+      continue;
+    }
     int64_t n = std::min(ckpt_every, n_steps - done);
     while (n > 0) {
       int m = (int)std::min<int64_t>(n, c->chunk);
@@ -3509,6 +3588,7 @@ wh_status wh_forward_ckpt(wh_ctx* c, int64_t n_steps, int64_t ckpt_every, void* 
   c->tape_steps = n_steps;
   c->tape_every = ckpt_every;
   c->tape_end = c->steps_done;
+  c->tape_last = T.n_seg > 0;
   return WH_OK;
 }
 
@@ -3519,24 +3599,15 @@ wh_status wh_adjoint_n(wh_ctx* c, void* tape, size_t tape_bytes, const double* g
   if (tape != c->tape || tape_bytes != c->tape_bytes || c->steps_done != c->tape_end)
     return fail(WH_ESTATE, "no matching wh_forward_ckpt for this tape (or steps taken since)");
   const int ns = c->P.ns;
-  TapeLayout T = tape_layout(ns, c->tape_steps, c->tape_every, tape_units(c));
+  const TapeLayout T = tape_layout(ns, c->tape_steps, c->tape_every, tape_units(c));
   double* ck = (double*)((char*)tape + T.ck);
   double* seg[2] = {(double*)((char*)tape + T.seg[0]), (double*)((char*)tape + T.seg[1])};
-  AdjParams q;
-  q.sp = step_params(c, 0);
+  AdjParams q = adj_params(c);
   q.tape = seg[0];
   q.grad = (double*)((char*)tape + T.grad);
   q.gQ_T = gQ_T; q.gV_T = gV_T;
   q.gQ_0 = gQ_0; q.gV_0 = gV_0; q.gm = gm; q.gm0 = gm0;
   q.ck = ck + (size_t)T.n_seg * 12 * ns;
-  q.n_seg = 0;
-  q.first_synced = 0;
-  q.sweep_waves = 0;
-  q.wide_record = c->wide_waves;
-  q.ck_rec = nullptr;
-  q.tape_rec = seg[1];
-  q.n_rec = 0;
-  q.rec_first_synced = 0;
   const bool gr = c->cfg.gr_c > 0;
   const bool kdk = c->cfg.scheme == WH_KDK;
   const bool jac = c->cfg.coords == WH_COORDS_JACOBI;
@@ -3571,50 +3642,21 @@ wh_status wh_adjoint_n(wh_ctx* c, void* tape, size_t tape_bytes, const double* g
       else hipLaunchKernelGGL((k_adj_init_kdk<false, 0>), g, b, 0, stream, q, synced_end);
     }
   }
-  auto seg_steps = [&](int64_t k) {
-    return (int)std::min<int64_t>(c->tape_every, c->tape_steps - k * c->tape_every);
-  };
-  auto set_record = [&](int64_t k) {   // segment k into tape k mod 2
-    q.ck_rec = ck + (size_t)k * 12 * ns;
-    q.tape_rec = seg[k & 1];
-    q.n_rec = seg_steps(k);
-    q.rec_first_synced = (k == 0);
-  };
-  const bool saba = c->cfg.scheme >= WH_SABA2;
-  auto launch = [&](int sweep_waves, int record_waves) {
-    q.sweep_waves = sweep_waves;
-    if (jac) {
-      const dim3 grid(sweep_waves + record_waves), block(64);
-      if (saba && gr) hipLaunchKernelGGL((k_adj_segment_jac<true, SCHEME_SABA>), grid, block, 0, stream, q);
-      else if (saba) hipLaunchKernelGGL((k_adj_segment_jac<false, SCHEME_SABA>), grid, block, 0, stream, q);
-      else if (kdk && gr) hipLaunchKernelGGL((k_adj_segment_jac<true, WH_KDK>), grid, block, 0, stream, q);
-      else if (kdk) hipLaunchKernelGGL((k_adj_segment_jac<false, WH_KDK>), grid, block, 0, stream, q);
-      else if (gr) hipLaunchKernelGGL((k_adj_segment_jac<true, WH_DKD>), grid, block, 0, stream, q);
-      else hipLaunchKernelGGL((k_adj_segment_jac<false, WH_DKD>), grid, block, 0, stream, q);
-      return;
-    }
-    if (saba) launch_adj_segment<false, SCHEME_SABA>(c, q, sweep_waves, record_waves, stream);
-    else if (kdk && gr) launch_adj_segment<true, WH_KDK>(c, q, sweep_waves, record_waves, stream);
-    else if (kdk) launch_adj_segment<false, WH_KDK>(c, q, sweep_waves, record_waves, stream);
-    else if (gr) launch_adj_segment<true, WH_DKD>(c, q, sweep_waves, record_waves, stream);
-    else launch_adj_segment<false, WH_DKD>(c, q, sweep_waves, record_waves, stream);
-  };
-  // record the last segment, then sweep segment k while recording k - 1
-  if (T.n_seg > 0) {
-    set_record(T.n_seg - 1);
-    launch(0, nw);
+  // sweep segment k while recording k - 1; the last one was recorded by the
+  // forward run, unless an earlier reverse pass of this tape has since used
+  // its buffer (a pass over three segments or more)
+  if (T.n_seg > 0 && !c->tape_last) {
+    set_record(q, (char*)tape, T, ns, c->tape_steps, c->tape_every, T.n_seg - 1);
+    launch_adj<false>(c, q, 0, nw, stream);
   }
   for (int64_t k = T.n_seg - 1; k >= 0; --k) {
     q.tape = seg[k & 1];
-    q.n_seg = seg_steps(k);
+    q.n_seg = (int)segment_steps(c->tape_steps, c->tape_every, k);
     q.first_synced = (k == 0);
-    if (k > 0) {
-      set_record(k - 1);
-      launch(nw, nw);
-    } else {
-      launch(nw, 0);
-    }
+    if (k > 0) set_record(q, (char*)tape, T, ns, c->tape_steps, c->tape_every, k - 1);
+    launch_adj<false>(c, q, nw, k > 0 ? nw : 0, stream);
   }
+  c->tape_last = T.n_seg > 0 && T.n_seg <= 2;
   if (jac) {
     q.ck = ck;   // the first checkpoint: the initial state the input transform is differentiated at
     if (c->cfg.gr_c > 0) hipLaunchKernelGGL(k_adj_in_jac<true>, dim3(nw), dim3(64), 0, stream, q);

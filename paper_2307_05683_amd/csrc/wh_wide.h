@@ -1,7 +1,7 @@
 // Four lanes per planet: how small ensembles run the one-planet step and the
 // split layout's.  VALU instructions per lane-step on eight-planet groups,
 // without and with GR: 271 and 303, and 15 LDS instructions (one lane per
-// planet: 474 and 522); in the split layout's order 273 and 301 (399 and 451).
+// planet: 474 and 522); in the split layout's order 273 and 301 (399 and 447).
 //
 // An ensemble with few wavefronts leaves most SIMDs idle, and a step's time is
 // then the instructions one wavefront issues.  Here a wavefront runs 16 planet
@@ -284,6 +284,23 @@ __device__ __forceinline__ void wide_kick(WideLane& L, const WideKick<G, STORAGE
   renorm(L.v, L.cv);
 }
 
+// The system's flags at a launch's end.
+template <int G>
+__device__ __forceinline__ void wide_flags(const StepParams& p, const WideLane& L, const KepDiag& dg, int lane) {
+  int f = 0;
+  if (L.pl >= 0) {
+    if (!__builtin_isfinite(L.q) || !__builtin_isfinite(L.v)) f |= WH_F_NONFINITE;
+    if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
+    if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
+  }
+  f |= dpp_i<DPP_QUAD_0>(f) | dpp_i<DPP_QUAD_1>(f) | dpp_i<DPP_QUAD_2>(f);   // the planet's three components
+  f = wide_or<G>(f);
+  if ((lane & (4 * G - 1)) == 0 && L.sys >= 0) {
+    p.flags[L.sys] |= (uint32_t)f;
+    p.synced[L.sys] = 0;
+  }
+}
+
 // step_lane for four lanes per planet (DHC).
 template <int G, bool GR, int SCHEME, int KC, int STORAGE>
 __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, double* block, int lane) {
@@ -326,18 +343,7 @@ __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, dou
       wide_drift<KC>(L, dt, dg);
     }
   }
-  int f = 0;
-  if (L.pl >= 0) {
-    if (!__builtin_isfinite(L.q) || !__builtin_isfinite(L.v)) f |= WH_F_NONFINITE;
-    if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
-    if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
-  }
-  f |= dpp_i<DPP_QUAD_0>(f) | dpp_i<DPP_QUAD_1>(f) | dpp_i<DPP_QUAD_2>(f);   // the planet's three components
-  f = wide_or<G>(f);
-  if ((lane & (4 * G - 1)) == 0 && L.sys >= 0) {
-    p.flags[L.sys] |= (uint32_t)f;
-    p.synced[L.sys] = 0;
-  }
+  wide_flags<G>(p, L, dg, lane);
 }
 
 // Slot of a lane's planet.  STORAGE 0: one planet per lane (the groups of
@@ -347,6 +353,24 @@ __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, dou
 template <int STORAGE> __device__ __forceinline__ int wide_slot(int w, int lane) {
   const int k = w * WIDE_SLOTS + (lane >> 2);
   return STORAGE == 1 ? 2 * k : k;
+}
+
+// Lanes 0..2 of a planet store their component; in the split packing's storage
+// both of a planet's slots, adjacent, take the value.
+template <int STORAGE> __device__ __forceinline__ void wide_put(double* row, double x) {
+  if (STORAGE == 1) *(double2*)row = make_double2(x, x);
+  else *row = x;
+}
+template <int STORAGE>
+__device__ __forceinline__ void wide_store(const StepParams& p, const WideLane& L, int slot, int c, int lane) {
+  if ((lane & 3) == 3) return;
+  const int ns = p.ns;
+  double* st = p.st + (size_t)c * ns + slot;
+  const size_t r3 = (size_t)3 * ns;
+  wide_put<STORAGE>(st, L.q);
+  wide_put<STORAGE>(st + r3, L.v);
+  wide_put<STORAGE>(st + 2 * r3 + ns, L.cq);
+  wide_put<STORAGE>(st + 3 * r3 + ns, L.cv);
 }
 
 template <int G, bool GR, int SCHEME, int KC, int STORAGE>
@@ -366,30 +390,14 @@ __device__ __forceinline__ void wide_group(const StepParams& p, int w, double* b
   L.pl = p.slot_pl[slot];
   L.first = L.sys >= 0 ? p.synced[L.sys] : 1;
   wide_steps<G, GR, SCHEME, KC, STORAGE>(p, L, block, lane);
-  if ((lane & 3) < 3) {
-    st[0] = L.q;
-    st[r3] = L.v;
-    st[2 * r3 + ns] = L.cq;
-    st[3 * r3 + ns] = L.cv;
-    if (STORAGE == 1) {
-      st[1] = L.q;
-      st[r3 + 1] = L.v;
-      st[2 * r3 + ns + 1] = L.cq;
-      st[3 * r3 + ns + 1] = L.cv;
-    }
-  }
+  wide_store<STORAGE>(p, L, slot, c, lane);
 }
 
 // Recording a segment of reverse mode (adj_record_lane of wh.hip, whose tape
 // rows it writes): the checkpoint's state through n_rec steps.  Lanes 0..2 of
-// a planet write the rows of their component, lane 3 the anomaly; in the split
-// packing's storage both of a planet's slots, adjacent, take the value.
-template <int STORAGE> __device__ __forceinline__ void wide_put(double* row, double x) {
-  if (STORAGE == 1) *(double2*)row = make_double2(x, x);
-  else *row = x;
-}
-
-template <int G, bool GR, int SCHEME, int STORAGE>
+// a planet write the rows of their component, lane 3 the anomaly.  FIN: the
+// run's last segment, stored as the context's state at its end.
+template <int G, bool GR, int SCHEME, int STORAGE, bool FIN>
 __device__ __forceinline__ void wide_record(const StepParams& p, const double* ck, double* tape, int n_rec,
                                             bool first_synced, int w, double* block, int lane) {
   const int slot = wide_slot<STORAGE>(w, lane), c = wide_comp(lane), ns = p.ns;
@@ -408,7 +416,7 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
   const bool comp = (lane & 3) < 3;
   WideKick<G, STORAGE> wk;
   wk.init(block, lane, L.m);
-  KepDiag dg{0.0, 1.0e300};   // not read
+  KepDiag dg{0.0, 1.0e300};
   double vk;
   double* row = tape + (size_t)c * ns + slot;         // the lane's rows: c, 3 + c, 7 + c
   double* xrow = tape + (size_t)6 * ns + slot;
@@ -452,6 +460,12 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
       wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, h, dt, h, vk);
       put_rest(X);
     }
+  }
+  if (FIN) {
+    L.sys = p.slot_sys[slot];
+    L.pl = p.slot_pl[slot];
+    wide_flags<G>(p, L, dg, lane);
+    wide_store<STORAGE>(p, L, slot, c, lane);
   }
 }
 
