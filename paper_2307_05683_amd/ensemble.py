@@ -50,6 +50,12 @@ class Ensemble:
         S = int(np_.shape[0])
         self.S = S
         self.n_planets = np_
+        # Outputs per planet are left untouched beyond a system's planets, so
+        # they start from zeros unless every system has eight; outputs per
+        # system are always written whole.  A fill took 4.4 us on the GPU, about
+        # as long as a small readout: 65536 systems, all outputs after 4 steps,
+        # 133 us with the fills and 113 without.
+        self._planet_array = torch.empty if bool((np_ == 8).all()) else torch.zeros
         cfg = _lib.default_config(S)
         cfg.gr_c = float(gr_c)
         cfg.scheme = SCHEMES[scheme]
@@ -112,31 +118,31 @@ class Ensemble:
 
     # ---- outputs (synchronized copies) -------------------------------------
     def state(self):
-        Q = torch.zeros((self.S, 8, 3), dtype=torch.float64, device=self.device)
-        V = torch.zeros((self.S, 8, 3), dtype=torch.float64, device=self.device)
+        Q = self._planet_array((self.S, 8, 3), dtype=torch.float64, device=self.device)
+        V = self._planet_array((self.S, 8, 3), dtype=torch.float64, device=self.device)
         check(_lib.load().wh_get_state(self._ctx, Q.data_ptr(), V.data_ptr(), _stream(self.device)))
         return Q, V
 
     def energy(self):
-        E = torch.zeros(self.S, dtype=torch.float64, device=self.device)
+        E = torch.empty(self.S, dtype=torch.float64, device=self.device)
         check(_lib.load().wh_energy(self._ctx, E.data_ptr(), _stream(self.device)))
         return E
 
     def elements(self):
         """Osculating heliocentric (a, e) of every planet: [S, 8] each."""
-        a = torch.zeros((self.S, 8), dtype=torch.float64, device=self.device)
-        e = torch.zeros((self.S, 8), dtype=torch.float64, device=self.device)
+        a = self._planet_array((self.S, 8), dtype=torch.float64, device=self.device)
+        e = self._planet_array((self.S, 8), dtype=torch.float64, device=self.device)
         check(_lib.load().wh_elements(self._ctx, a.data_ptr(), e.data_ptr(), _stream(self.device)))
         return a, e
 
     def angular_momentum(self):
         """Total angular momentum sum_i Q_i x m_i V_i of every system: [S, 3]."""
-        L = torch.zeros((self.S, 3), dtype=torch.float64, device=self.device)
+        L = torch.empty((self.S, 3), dtype=torch.float64, device=self.device)
         check(_lib.load().wh_angular_momentum(self._ctx, L.data_ptr(), _stream(self.device)))
         return L
 
     def flags(self):
-        f = torch.zeros(self.S, dtype=torch.int32, device=self.device)
+        f = torch.empty(self.S, dtype=torch.int32, device=self.device)
         check(_lib.load().wh_status_flags(self._ctx, f.data_ptr(), _stream(self.device)))
         return f
 
@@ -186,10 +192,10 @@ class Ensemble:
         _, ptr, nbytes = self._tape
         gQ_T = _dev_f64(gQ_T, self.device)
         gV_T = _dev_f64(gV_T, self.device)
-        gQ0 = torch.zeros((self.S, 8, 3), dtype=torch.float64, device=self.device)
-        gV0 = torch.zeros_like(gQ0)
-        gm = torch.zeros((self.S, 8), dtype=torch.float64, device=self.device)
-        gm0 = torch.zeros(self.S, dtype=torch.float64, device=self.device)
+        gQ0 = self._planet_array((self.S, 8, 3), dtype=torch.float64, device=self.device)
+        gV0 = self._planet_array((self.S, 8, 3), dtype=torch.float64, device=self.device)
+        gm = self._planet_array((self.S, 8), dtype=torch.float64, device=self.device)
+        gm0 = torch.empty(self.S, dtype=torch.float64, device=self.device)
         check(_lib.load().wh_adjoint_n(self._ctx, ptr, nbytes, gQ_T.data_ptr(), gV_T.data_ptr(), gQ0.data_ptr(),
                                        gV0.data_ptr(), gm.data_ptr(), gm0.data_ptr(), _stream(self.device)))
         return gQ0, gV0, gm, gm0
