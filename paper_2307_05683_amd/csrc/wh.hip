@@ -30,6 +30,7 @@
 #include "wh_split.h"
 #include "wh_step.h"
 #include "wh_wide.h"
+#include "wh_wide_adjoint.h"
 #include "wh_host.h"
 
 using namespace wh;
@@ -1234,7 +1235,7 @@ struct AdjParams {
   int n_seg;           // steps of the segment being swept
   int first_synced;    // it starts from the synchronized initial state
   int sweep_waves;     // wavefronts of the sweeping role (0: the launch only records)
-  int wide_record;     // wavefronts of the recording role with four lanes per planet (0: a lane each)
+  int wide_waves;      // wavefronts of each role with four lanes per planet (0: a lane per planet)
   const double* ck_rec;  // recording role: checkpoint of the segment to record,
   double* tape_rec;      // the tape to fill,
   int n_rec;             // its steps,
@@ -1829,23 +1830,33 @@ template <bool GR, int SCH, bool FIN> __global__ __launch_bounds__(256) void k_a
 
 // Waves [0, sweep_waves) sweep one segment, the waves after them record the
 // previous segment; each role covers the packing's waves once.  Contexts whose
-// step runs with four lanes per planet record in that form too (the same bits
-// as the step, which recording repeats).
+// step runs with four lanes per planet record (the same bits as the step,
+// which recording repeats) and sweep in that form too.
 template <bool GR, bool SPLIT, int SCH, bool FIN> __global__ __launch_bounds__(64) void k_adj_segment(AdjParams q) {
-  __shared__ double lds[WIDE_LDS];
+  __shared__ double lds[WIDE_ADJ_LDS];
   const StepParams& p = q.sp;
   const int lane = threadIdx.x;
   int wave = (int)blockIdx.x;
   const bool sweep = !FIN && wave < q.sweep_waves;
   if (!sweep) wave -= q.sweep_waves;
-  if (!sweep && q.wide_record > 0) {
-    if (wave >= q.wide_record) return;
-    const bool first = q.rec_first_synced != 0;
-    if (SPLIT) wide_record<8, GR, SCH, 1, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else if (wave < 4 * p.w1) wide_record<1, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else if (wave < 4 * p.w2) wide_record<2, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else if (wave < 4 * p.w4) wide_record<4, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
-    else wide_record<8, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, q.n_rec, first, wave, lds, lane);
+  const int ww = q.wide_waves;
+  if (ww > 0) {
+    if (wave >= ww) return;
+    if (sweep) {
+      const bool first = q.first_synced != 0;
+      if (SPLIT) wide_sweep<8, GR, SCH, 1>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
+      else if (wave < 4 * p.w1) wide_sweep<1, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
+      else if (wave < 4 * p.w2) wide_sweep<2, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
+      else if (wave < 4 * p.w4) wide_sweep<4, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
+      else wide_sweep<8, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
+    } else {
+      const bool first = q.rec_first_synced != 0;
+      if (SPLIT) wide_record<8, GR, SCH, 1, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
+      else if (wave < 4 * p.w1) wide_record<1, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
+      else if (wave < 4 * p.w2) wide_record<2, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
+      else if (wave < 4 * p.w4) wide_record<4, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
+      else wide_record<8, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
+    }
     return;
   }
   if (wave >= p.w8) return;
@@ -3162,22 +3173,22 @@ int tape_units(const wh_ctx* c) { return c->cfg.scheme >= WH_SABA2 ? c->cfg.sche
 // the packing; the serial packing records with one thread per 8-slot group).
 // FIN: the forward run's last segment, recorded and stored as its end.
 template <bool GR, int SCH, bool FIN>
-void launch_adj_segment(const wh_ctx* c, const AdjParams& q, int sweep_waves, int record_waves, hipStream_t st) {
+void launch_adj_segment(const wh_ctx* c, const AdjParams& q, int record_waves, hipStream_t st) {
   if (c->P.serial) {
     const int rec = record_waves > 0 ? (record_waves * 8 + 63) / 64 : 0;
-    const dim3 grid(sweep_waves + rec), block(64);
+    const dim3 grid(q.sweep_waves + rec), block(64);
     const size_t smem = SERIAL_LDS_PER_WAVE * sizeof(double);
     hipLaunchKernelGGL((k_adj_segment_serial<GR, SCH, FIN>), grid, block, smem, st, q);
     return;
   }
-  const dim3 grid(sweep_waves + (record_waves > 0 && c->wide_waves > 0 ? c->wide_waves : record_waves)), block(64);
+  const dim3 grid(q.sweep_waves + (record_waves > 0 && c->wide_waves > 0 ? c->wide_waves : record_waves)), block(64);
   if (c->P.pair) hipLaunchKernelGGL((k_adj_segment_pair<GR, SCH, FIN>), grid, block, 0, st, q);
   else if (c->P.split) hipLaunchKernelGGL((k_adj_segment<GR, true, SCH, FIN>), grid, block, 0, st, q);
   else hipLaunchKernelGGL((k_adj_segment<GR, false, SCH, FIN>), grid, block, 0, st, q);
 }
 template <bool FIN>
 void launch_adj(const wh_ctx* c, AdjParams& q, int sweep_waves, int record_waves, hipStream_t st) {
-  q.sweep_waves = sweep_waves;
+  q.sweep_waves = sweep_waves > 0 && c->wide_waves > 0 ? c->wide_waves : sweep_waves;
   const bool gr = c->cfg.gr_c > 0, kdk = c->cfg.scheme == WH_KDK, saba = c->cfg.scheme >= WH_SABA2;
   if (c->cfg.coords == WH_COORDS_JACOBI) {
     const dim3 grid(sweep_waves + record_waves), block(64);
@@ -3189,11 +3200,11 @@ void launch_adj(const wh_ctx* c, AdjParams& q, int sweep_waves, int record_waves
     else hipLaunchKernelGGL((k_adj_segment_jac<false, WH_DKD, FIN>), grid, block, 0, st, q);
     return;
   }
-  if (saba) launch_adj_segment<false, SCHEME_SABA, FIN>(c, q, sweep_waves, record_waves, st);
-  else if (kdk && gr) launch_adj_segment<true, WH_KDK, FIN>(c, q, sweep_waves, record_waves, st);
-  else if (kdk) launch_adj_segment<false, WH_KDK, FIN>(c, q, sweep_waves, record_waves, st);
-  else if (gr) launch_adj_segment<true, WH_DKD, FIN>(c, q, sweep_waves, record_waves, st);
-  else launch_adj_segment<false, WH_DKD, FIN>(c, q, sweep_waves, record_waves, st);
+  if (saba) launch_adj_segment<false, SCHEME_SABA, FIN>(c, q, record_waves, st);
+  else if (kdk && gr) launch_adj_segment<true, WH_KDK, FIN>(c, q, record_waves, st);
+  else if (kdk) launch_adj_segment<false, WH_KDK, FIN>(c, q, record_waves, st);
+  else if (gr) launch_adj_segment<true, WH_DKD, FIN>(c, q, record_waves, st);
+  else launch_adj_segment<false, WH_DKD, FIN>(c, q, record_waves, st);
 }
 
 // The parameters of a context's reverse pass that do not change from launch
@@ -3203,7 +3214,7 @@ AdjParams adj_params(const wh_ctx* c) {
   AdjParams q;
   memset(&q, 0, sizeof(q));
   q.sp = step_params(c, 0);
-  q.wide_record = c->wide_waves;
+  q.wide_waves = c->wide_waves;
   return q;
 }
 int64_t segment_steps(int64_t n_steps, int64_t every, int64_t k) { return std::min<int64_t>(every, n_steps - k * every); }

@@ -55,17 +55,15 @@ __device__ __forceinline__ void kepler_at_X(double qx, double qy, double qz, dou
 // F_beta dbeta) / F_X with F_X = r, F_r0 = X, F_eta = G2, F_zeta = G3 and
 // F_beta = eta dG2/dbeta + zeta dG3/dbeta, where dG_n/dbeta =
 // (n G_{n+2} - X G_{n+1}) / 2 and dG_n/dX = G_{n-1}.
-__device__ __forceinline__ void kepler_vjp(const KepFwd& k, double qx, double qy, double qz, double vx, double vy,
-                                           double vz, double mu, double& gqx, double& gqy, double& gqz,
-                                           double& gvx, double& gvy, double& gvz, double& gmu) {
+// The scalars of it, from the products of the output's adjoint with the drift's
+// start: gf = gQ1.Q, gg = gQ1.V, gfd = gV1.Q, ggd = gV1.V.  Then
+//   gQ = f gQ1 + f' gV1 + eta V + q Q,   gV = g gQ1 + g' gV1 + eta Q + v V.
+struct KepAdj {
+  double eta, q, v, mu;
+};
+__device__ __forceinline__ KepAdj kepler_adj(const KepFwd& k, double gf, double gg, double gfd, double ggd,
+                                             double mu) {
   const double* G = k.G;
-  // outputs Q1 = f Q + g V, V1 = f' Q + g' V
-  double gf = gqx * qx + gqy * qy + gqz * qz;
-  double gg = gqx * vx + gqy * vy + gqz * vz;
-  double gfd = gvx * qx + gvy * qy + gvz * qz;
-  double ggd = gvx * vx + gvy * vy + gvz * vz;
-  double nqx = k.f * gqx + k.fd * gvx, nqy = k.f * gqy + k.fd * gvy, nqz = k.f * gqz + k.fd * gvz;
-  double nvx = k.g * gqx + k.gd * gvx, nvy = k.g * gqy + k.gd * gvy, nvz = k.g * gqz + k.gd * gvz;
   // f = 1 - mu G2/r0, g = tau - mu G3, f' = -mu G1/(r0 r), g' = 1 - mu G2/r
   const double ir0 = k.ir0, ir = k.ir;
   const double a0 = gf * ir0, a1 = ggd * ir, b = gfd * (ir0 * ir);
@@ -104,17 +102,28 @@ __device__ __forceinline__ void kepler_vjp(const KepFwd& k, double qx, double qy
   const double gb = 2.0 * gbeta * ir0;
   gm += gb;
   gr0 -= gb * mu * ir0;
-  // eta = Q.V, |V|^2, r0 = |Q|
-  const double gq = gr0 * ir0, gv = -2.0 * gbeta;
-  nqx += geta * vx + gq * qx;
-  nqy += geta * vy + gq * qy;
-  nqz += geta * vz + gq * qz;
-  nvx += geta * qx + gv * vx;
-  nvy += geta * qy + gv * vy;
-  nvz += geta * qz + gv * vz;
+  return KepAdj{geta, gr0 * ir0, -2.0 * gbeta, gm};
+}
+
+__device__ __forceinline__ void kepler_vjp(const KepFwd& k, double qx, double qy, double qz, double vx, double vy,
+                                           double vz, double mu, double& gqx, double& gqy, double& gqz,
+                                           double& gvx, double& gvy, double& gvz, double& gmu) {
+  // outputs Q1 = f Q + g V, V1 = f' Q + g' V
+  const double gf = gqx * qx + gqy * qy + gqz * qz;
+  const double gg = gqx * vx + gqy * vy + gqz * vz;
+  const double gfd = gvx * qx + gvy * qy + gvz * qz;
+  const double ggd = gvx * vx + gvy * vy + gvz * vz;
+  const KepAdj a = kepler_adj(k, gf, gg, gfd, ggd, mu);
+  // and through eta = Q.V, |V|^2 and r0 = |Q|
+  const double nqx = k.f * gqx + k.fd * gvx + (a.eta * vx + a.q * qx);
+  const double nqy = k.f * gqy + k.fd * gvy + (a.eta * vy + a.q * qy);
+  const double nqz = k.f * gqz + k.fd * gvz + (a.eta * vz + a.q * qz);
+  const double nvx = k.g * gqx + k.gd * gvx + (a.eta * qx + a.v * vx);
+  const double nvy = k.g * gqy + k.gd * gvy + (a.eta * qy + a.v * vy);
+  const double nvz = k.g * gqz + k.gd * gvz + (a.eta * qz + a.v * vz);
   gqx = nqx; gqy = nqy; gqz = nqz;
   gvx = nvx; gvy = nvy; gvz = nvz;
-  gmu += gm;
+  gmu += a.mu;
 }
 
 // Adjoint of the interaction kick V += tau a(Q) inside a group, with the DPP

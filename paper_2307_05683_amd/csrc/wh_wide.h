@@ -393,82 +393,6 @@ __device__ __forceinline__ void wide_group(const StepParams& p, int w, double* b
   wide_store<STORAGE>(p, L, slot, c, lane);
 }
 
-// Recording a segment of reverse mode (adj_record_lane of wh.hip, whose tape
-// rows it writes): the checkpoint's state through n_rec steps.  Lanes 0..2 of
-// a planet write the rows of their component, lane 3 the anomaly.  FIN: the
-// run's last segment, stored as the context's state at its end.
-template <int G, bool GR, int SCHEME, int STORAGE, bool FIN>
-__device__ __forceinline__ void wide_record(const StepParams& p, const double* ck, double* tape, int n_rec,
-                                            bool first_synced, int w, double* block, int lane) {
-  const int slot = wide_slot<STORAGE>(w, lane), c = wide_comp(lane), ns = p.ns;
-  const size_t r3 = (size_t)3 * ns, step_rows = (size_t)wh_host::WH_TAPE_ROWS * ns;
-  const double* cs = ck + (size_t)c * ns + slot;
-  WideLane L{};
-  L.q = cs[0];
-  L.v = cs[r3];
-  L.cq = cs[2 * r3];
-  L.cv = cs[3 * r3];
-  L.m = p.st[(size_t)6 * ns + slot];
-  L.m0 = p.m0s[slot];
-  const double dt = p.dts[slot], h = 0.5 * dt;
-  const double inv_m0 = 1.0 / L.m0;
-  const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
-  const bool comp = (lane & 3) < 3;
-  WideKick<G, STORAGE> wk;
-  wk.init(block, lane, L.m);
-  KepDiag dg{0.0, 1.0e300};
-  double vk;
-  double* row = tape + (size_t)c * ns + slot;         // the lane's rows: c, 3 + c, 7 + c
-  double* xrow = tape + (size_t)6 * ns + slot;
-  auto put_state = [&]() {
-    if (comp) { wide_put<STORAGE>(row, L.q); wide_put<STORAGE>(row + r3, L.v); }
-  };
-  auto put_rest = [&](double X) {
-    if (comp) wide_put<STORAGE>(row + 2 * r3 + ns, vk);
-    else wide_put<STORAGE>(xrow, X);
-    row += step_rows;
-    xrow += step_rows;
-  };
-  if constexpr (SCHEME == SCHEME_SABA) {
-    const int nu = p.saba_n;
-    const double c1dt = p.sc[0] * dt;
-    for (int s = 0; s < n_rec; ++s)
-      for (int k = 0; k < nu; ++k) {
-        const double tau = k > 0 ? p.sc[k] * dt : (first_synced && s == 0 ? c1dt : 2.0 * c1dt);
-        const double tb = p.sd[k] * dt;
-        put_state();
-        const double X = wide_drift<0>(L, tau, dg);
-        wide_kick<G, false, STORAGE>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
-        put_rest(X);
-      }
-  } else if constexpr (SCHEME == WH_KDK) {
-    double ta = first_synced ? 0.0 : h;
-    double ti = first_synced ? h : dt;
-    for (int s = 0; s < n_rec; ++s) {
-      put_state();
-      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, ta, ti, h, vk);
-      ta = h;
-      ti = dt;
-      put_rest(wide_drift<0>(L, dt, dg));
-    }
-  } else {
-    double tk = first_synced ? h : dt;
-    for (int s = 0; s < n_rec; ++s) {
-      put_state();
-      const double X = wide_drift<0>(L, tk, dg);
-      tk = dt;
-      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, h, dt, h, vk);
-      put_rest(X);
-    }
-  }
-  if (FIN) {
-    L.sys = p.slot_sys[slot];
-    L.pl = p.slot_pl[slot];
-    wide_flags<G>(p, L, dg, lane);
-    wide_store<STORAGE>(p, L, slot, c, lane);
-  }
-}
-
 // The persistent step kernel of this form, defined and instantiated in
 // wh_wide_step.hip.  Up to four wavefronts per workgroup.
 template <bool GR, int SCHEME, int KC, int STORAGE>
