@@ -1374,6 +1374,7 @@ __device__ void adj_record_lane(const AdjParams& q, int slot, int lane) {
   const double inv_m0 = 1.0 / L.m0;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
   KepDiag dg{0.0, 1.0e300};
+  wait_loads();
   if constexpr (SCH == SCHEME_SABA) {
     // SABA_n: n units per step, unit k = K(tau_k) then the perturbation kick
     // B(d_k dt); tau_0 = c_1 dt (2 c_1 dt after the first step), tau_k = c_{k+1} dt
@@ -1603,6 +1604,7 @@ __device__ void adj_record_pair(const AdjParams& q, int sa, int lane) {
   const double inv_m0 = 1.0 / A.m0;
   const double kg = GR ? p.kgr * A.m0 * A.m0 : 0.0;
   KepDiag dga{0.0, 1.0e300}, dgb{0.0, 1.0e300};
+  wait_loads();
   if constexpr (SCH == SCHEME_SABA) {
     const int nu = p.saba_n;
     const double c1dt = p.sc[0] * dt;
@@ -1919,6 +1921,7 @@ __device__ void adj_record_serial(const AdjParams& q, int base, int n, double* c
   const double inv_m0 = 1.0 / m0;
   const double kg = GR ? p.kgr * m0 * m0 : 0.0;
   KepDiag dg{0.0, 1.0e300};
+  wait_loads();
   if constexpr (SCH == SCHEME_SABA) {
     const int nu = p.saba_n;
     const double c1dt = p.sc[0] * dt;
@@ -2204,6 +2207,7 @@ __device__ void adj_record_jac(const AdjParams& q, int slot, int lane) {
   const double dt = p.dts[slot], h = 0.5 * dt;
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
   KepDiag dg{0.0, 1.0e300};
+  wait_loads();
   auto put_state = [&](double* row) {
     row[0] = L.qx; row[ns] = L.qy; row[2 * ns] = L.qz;
     row[3 * ns] = L.vx; row[4 * ns] = L.vy; row[5 * ns] = L.vz;

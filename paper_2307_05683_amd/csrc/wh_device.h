@@ -11,6 +11,12 @@
 
 namespace wh {
 
+// Waits for the wavefront's loads.  For a loop that stores: loads still in
+// flight at its head make the compiler wait inside it, and those waits, on the
+// counter that stores share, take in the stores of the steps before.  (A
+// one-system recording, 250 steps of 8 planets: 260 -> 216 us.)
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0) alone
+
 // ---------------------------------------------------------------------------
 // Reciprocal and reciprocal square root.  The hardware seeds (v_rcp_f64,
 // v_rsq_f64) are good to about 2^-24; one Newton step with the second-order

@@ -45,6 +45,7 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
   WideKick<G, STORAGE> wk;
   wk.init(block, lane, L.m);
   KepDiag dg{0.0, 1.0e300};
+  wait_loads();
   double vk;
   double* row = tape + (size_t)w * WIDE_TAPE + (lane >> 2);
   const size_t step = (size_t)n_waves * WIDE_TAPE;
