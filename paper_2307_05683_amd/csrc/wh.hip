@@ -2975,6 +2975,11 @@ void launch_step_kernel(const wh_ctx* c, const StepParams& p, int n_waves, hipSt
 // The step with four lanes per planet (wh_wide.h).
 template <int STORAGE> const void* wide_kernel_of(const wh_ctx* c) {
   const bool gr = c->cfg.gr_c > 0, dkd = c->cfg.scheme == WH_DKD;
+  if (c->cfg.coords == WH_COORDS_JACOBI) {
+    if (c->cfg.scheme >= WH_SABA2) return gr ? (const void*)k_step_wide<true, SCHEME_SABA, 0, 0, true> : (const void*)k_step_wide<false, SCHEME_SABA, 0, 0, true>;
+    if (dkd) return gr ? (const void*)k_step_wide<true, WH_DKD, 0, 0, true> : (const void*)k_step_wide<false, WH_DKD, 0, 0, true>;
+    return gr ? (const void*)k_step_wide<true, WH_KDK, 0, 0, true> : (const void*)k_step_wide<false, WH_KDK, 0, 0, true>;
+  }
   if (c->cfg.scheme >= WH_SABA2) return (const void*)k_step_wide<false, SCHEME_SABA, 0, STORAGE>;
   if (c->cfg.kepler_counts == 1) {
     if (dkd) return gr ? (const void*)k_step_wide<true, WH_DKD, 1, STORAGE> : (const void*)k_step_wide<false, WH_DKD, 1, STORAGE>;
@@ -2991,7 +2996,7 @@ void launch_wide(const wh_ctx* c, const StepParams& p, hipStream_t st) {
 }
 
 // Whether the step runs with four lanes per planet: in the one-planet and
-// split packings of a DHC context with the DPP exchange, while its
+// split packings of a context with the DPP exchange, while its
 // wavefronts (four times the one-planet packing's, twice the split packing's)
 // are no more than the GPU has SIMDs: there the wavefront's own instructions
 // set the time, beyond it the sum of all.  Eight-planet systems without GR, us
@@ -2999,11 +3004,12 @@ void launch_wide(const wh_ctx* c, const StepParams& p, hipStream_t st) {
 // and 0.78), 2048 systems, a wavefront per SIMD, 0.74 and 0.97 (0.77 and 0.80);
 // at 3072, 1.5 per SIMD, it would take 1.12 against 0.96.  Four planets: 4096
 // systems 0.65 and 0.75, 8192 systems 1.06 and 0.78; two planets: 8192 systems
-// 0.58 and 0.65, 16384 systems 0.98 and 0.67.
+// 0.58 and 0.65, 16384 systems 0.98 and 0.67.  In Jacobi coordinates: 2048
+// systems of eight 1.05 and 1.41, 2600 both 1.40; 4096 systems of four 0.76 and
+// 1.08, 6144 both 1.08.
 wh_status choose_wide(wh_ctx* c) {
   c->wide_waves = 0;
-  if (c->cfg.coords != WH_COORDS_DHC || c->P.pair || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP)
-    return WH_OK;
+  if (c->P.pair || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP) return WH_OK;
   int dev = 0, ncu = 0;
   wh_status st;
   if ((st = hip_check(hipGetDevice(&dev), "hipGetDevice")) ||
@@ -3185,14 +3191,14 @@ void launch_adj_segment(const wh_ctx* c, const AdjParams& q, int record_waves, h
     hipLaunchKernelGGL((k_adj_segment_serial<GR, SCH, FIN>), grid, block, smem, st, q);
     return;
   }
-  const dim3 grid(q.sweep_waves + (record_waves > 0 && c->wide_waves > 0 ? c->wide_waves : record_waves)), block(64);
+  const dim3 grid(q.sweep_waves + (record_waves > 0 && q.wide_waves > 0 ? q.wide_waves : record_waves)), block(64);
   if (c->P.pair) hipLaunchKernelGGL((k_adj_segment_pair<GR, SCH, FIN>), grid, block, 0, st, q);
   else if (c->P.split) hipLaunchKernelGGL((k_adj_segment<GR, true, SCH, FIN>), grid, block, 0, st, q);
   else hipLaunchKernelGGL((k_adj_segment<GR, false, SCH, FIN>), grid, block, 0, st, q);
 }
 template <bool FIN>
 void launch_adj(const wh_ctx* c, AdjParams& q, int sweep_waves, int record_waves, hipStream_t st) {
-  q.sweep_waves = sweep_waves > 0 && c->wide_waves > 0 ? c->wide_waves : sweep_waves;
+  q.sweep_waves = sweep_waves > 0 && q.wide_waves > 0 ? q.wide_waves : sweep_waves;
   const bool gr = c->cfg.gr_c > 0, kdk = c->cfg.scheme == WH_KDK, saba = c->cfg.scheme >= WH_SABA2;
   if (c->cfg.coords == WH_COORDS_JACOBI) {
     const dim3 grid(sweep_waves + record_waves), block(64);
@@ -3218,7 +3224,7 @@ AdjParams adj_params(const wh_ctx* c) {
   AdjParams q;
   memset(&q, 0, sizeof(q));
   q.sp = step_params(c, 0);
-  q.wide_waves = c->wide_waves;
+  q.wide_waves = c->cfg.coords == WH_COORDS_DHC ? c->wide_waves : 0;   // Jacobi contexts: a lane per planet
   return q;
 }
 int64_t segment_steps(int64_t n_steps, int64_t every, int64_t k) { return std::min<int64_t>(every, n_steps - k * every); }

@@ -2,6 +2,8 @@
 // split layout's.  VALU instructions per lane-step on eight-planet groups,
 // without and with GR: 271 and 303, and 15 LDS instructions (one lane per
 // planet: 474 and 522); in the split layout's order 273 and 301 (399 and 447).
+// In Jacobi coordinates, on groups of 8, 4 and 2 planets: 418, 325 and 302
+// (671, 529 and 447).
 //
 // An ensemble with few wavefronts leaves most SIMDs idle, and a step's time is
 // then the instructions one wavefront issues.  Here a wavefront runs 16 planet
@@ -243,14 +245,14 @@ struct WideLane {
 
 __device__ __forceinline__ int wide_comp(int lane) { return (lane & 3) == 3 ? 0 : lane & 3; }
 
-// Kepler drift (drift of wh_step.h): the whole planet's coefficients, the
-// lane's component of the map.  Returns the anomaly.
+// Kepler drift (drift of wh_step.h) about mass mu: the whole planet's
+// coefficients, the lane's component of the map.  Returns the anomaly.
 template <int KC>
-__device__ __forceinline__ double wide_drift(WideLane& L, double tau, KepDiag& dg) {
+__device__ __forceinline__ double wide_drift(WideLane& L, double mu, double tau, KepDiag& dg) {
   KepCoef k;
   const double X = kepler_coeffs<KepSet<KC>::NH, KepSet<KC>::NN, KepSet<KC>::KH, KepSet<KC>::KN>(
       dpp<DPP_QUAD_0>(L.q), dpp<DPP_QUAD_1>(L.q), dpp<DPP_QUAD_2>(L.q), dpp<DPP_QUAD_0>(L.v), dpp<DPP_QUAD_1>(L.v),
-      dpp<DPP_QUAD_2>(L.v), L.m0, tau, dg, k);
+      dpp<DPP_QUAD_2>(L.v), mu, tau, dg, k);
   double hq, lq, hv, lv;
   lin2_dd(k.fm1, L.q, k.g, L.v, hq, lq);
   lin2_dd(k.gdm1, L.v, k.fd, L.q, hv, lv);
@@ -284,6 +286,92 @@ __device__ __forceinline__ void wide_kick(WideLane& L, const WideKick<G, STORAGE
   renorm(L.v, L.cv);
 }
 
+// Group scans of a component over planets (group_scan_incl and the others of
+// wh_device.h): planet p's neighbour n places on is 4n lanes on in its row;
+// in a group of two rows, also in the other row, found by rotating both.
+// DOWN: reads planet p + n, else p - n.
+template <int G, int N, bool DOWN> __device__ __forceinline__ double wide_shift(double v) {
+  if (G <= 4) return dpp<(DOWN ? 0x100 : 0x110) + 4 * N>(v);
+  const double t = N == 4 ? v : dpp<0x120 + (DOWN ? 16 - 4 * (N & 3) : 4 * (N & 3))>(v);
+  int l0, l1, h0, h1;
+  row_pair(__double2loint(t), l0, l1);
+  row_pair(__double2hiint(t), h0, h1);
+  const int r = (threadIdx.x >> 2) & 3;
+  const bool odd = threadIdx.x & 16;
+  if (DOWN) return odd || r + N >= 4 ? __hiloint2double(h1, l1) : __hiloint2double(h0, l0);
+  return odd && r >= N ? __hiloint2double(h1, l1) : __hiloint2double(h0, l0);
+}
+template <int G> __device__ __forceinline__ double wide_scan_excl(double v, int p) {
+  if (G == 1) return 0.0;
+  double t = wide_shift<G, 1, false>(v);
+  v = p >= 1 ? t : 0.0;
+  t = wide_shift<G, 1, false>(v);
+  v += p >= 1 ? t : 0.0;
+  if (G >= 4) { t = wide_shift<G, 2, false>(v); v += p >= 2 ? t : 0.0; }
+  if (G >= 8) { t = wide_shift<G, 4, false>(v); v += p >= 4 ? t : 0.0; }
+  return v;
+}
+// v: the sum over the planet and the next one
+template <int G> __device__ __forceinline__ double wide_suffix_rest(double v, int p) {
+  if (G >= 4) { const double t = wide_shift<G, 2, true>(v); v += p + 2 < G ? t : 0.0; }
+  if (G >= 8) { const double t = wide_shift<G, 4, true>(v); v += p + 4 < G ? t : 0.0; }
+  return v;
+}
+template <int G> __device__ __forceinline__ double wide_suffix_excl(double v, int p) {
+  if (G == 1) return 0.0;
+  double t = wide_shift<G, 1, true>(v);
+  v = p + 1 < G ? t : 0.0;
+  t = wide_shift<G, 1, true>(v);
+  v += p + 1 < G ? t : 0.0;
+  return wide_suffix_rest<G>(v, p);
+}
+
+// The planet's constants in Jacobi coordinates (jac_const) and the kick there
+// (kick_jacobi) on the lane's component.
+struct WideJac {
+  double Mi, inv_Mim1, w, ratio;
+  int p;
+};
+template <int G> __device__ __forceinline__ WideJac wide_jac(double m0, double m, int lane) {
+  WideJac c;
+  c.p = (lane >> 2) & (G - 1);
+  const double Mim1 = m0 + wide_scan_excl<G>(m, c.p);
+  c.Mi = Mim1 + m;
+  c.inv_Mim1 = 1.0 / Mim1;
+  c.w = m / c.Mi;
+  c.ratio = m0 / Mim1;
+  return c;
+}
+template <int G, bool GR>
+__device__ __forceinline__ void wide_kick_jacobi(WideLane& L, const WideKick<G, 0>& wk, const WideJac& jc, double kg,
+                                                 double tau) {
+#pragma clang fp contract(off)
+  const double q = L.q + wide_scan_excl<G>(jc.w * L.q, jc.p);
+  double x, y, z;
+  const double a = wk.accel(q, x, y, z);
+  const double jx = dpp<DPP_QUAD_0>(L.q), jy = dpp<DPP_QUAD_1>(L.q), jz = dpp<DPP_QUAD_2>(L.q);
+  const double irq3 = rsqrt3_full(fma(x, x, fma(y, y, z * z)));
+  const double kp = jc.Mi * rsqrt3_full(fma(jx, jx, fma(jy, jy, jz * jz)));
+  const double kq = (jc.Mi * jc.ratio) * irq3;
+  const double wq = L.m * irq3;
+  const double c = fma(jc.ratio, wide_suffix_excl<G>(wq * q, jc.p), wide_scan_excl<G>(L.m * a, jc.p) * jc.inv_Mim1);
+  const double s = (a - c) + (kp * L.q - kq * q);
+  if (GR) {
+    const double ir2 = rcp_full(fma(x, x, fma(y, y, z * z)));   // gr_accel
+    const double g = (-kg * ir2 * ir2) * q;
+    double u = L.m * g;
+    if (G >= 2) {
+      const double t = wide_shift<G, 1, true>(u);
+      u = wide_suffix_rest<G>(fma(L.m, g, jc.p + 1 < G ? t : 0.0), jc.p);
+    }
+    L.cv += fma(tau, fma(u, jc.inv_Mim1, g), tau * s);
+  } else {
+    L.cv = fma(tau, s, L.cv);
+  }
+  renorm(L.q, L.cq);
+  renorm(L.v, L.cv);
+}
+
 // The system's flags at a launch's end.
 template <int G>
 __device__ __forceinline__ void wide_flags(const StepParams& p, const WideLane& L, const KepDiag& dg, int lane) {
@@ -301,8 +389,8 @@ __device__ __forceinline__ void wide_flags(const StepParams& p, const WideLane& 
   }
 }
 
-// step_lane for four lanes per planet (DHC).
-template <int G, bool GR, int SCHEME, int KC, int STORAGE>
+// step_lane for four lanes per planet.
+template <int G, bool GR, int SCHEME, int KC, int STORAGE, bool JAC>
 __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, double* block, int lane) {
   WideKick<G, STORAGE> wk;
   wk.init(block, lane, L.m);
@@ -311,6 +399,9 @@ __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, dou
   const double kg = GR ? p.kgr * L.m0 * L.m0 : 0.0;
   KepDiag dg{0.0, 1.0e300};
   double vk;
+  WideJac jc{};
+  if constexpr (JAC) jc = wide_jac<G>(L.m0, L.m, lane);
+  const double mu = JAC ? jc.Mi : L.m0;
   const int n_steps = p.n_steps;
   if constexpr (SCHEME == SCHEME_SABA) {
     const double c1dt = p.sc[0] * dt;
@@ -320,27 +411,30 @@ __device__ __forceinline__ void wide_steps(const StepParams& p, WideLane& L, dou
     for (int s = 0; s < n_steps; ++s) {
 #pragma unroll 1
       for (int k = 0; k < n_units; ++k) {
-        wide_drift<0>(L, tk, dg);
+        wide_drift<0>(L, mu, tk, dg);
         const double tb = (k == 0 ? sd0 : k == 1 ? sd1 : k == 2 ? sd2 : sd3) * dt;
-        wide_kick<G, false, STORAGE>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
+        if constexpr (JAC) wide_kick_jacobi<G, GR>(L, wk, jc, kg, tb);
+        else wide_kick<G, false, STORAGE>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
         tk = k + 1 < n_units ? (k == 0 ? sc1 : k == 1 ? sc2 : sc3) * dt : 2.0 * c1dt;
       }
     }
   } else if (SCHEME == WH_DKD) {
     double tk = L.first ? h : dt;
     for (int s = 0; s < n_steps; ++s) {
-      wide_drift<KC>(L, tk, dg);
+      wide_drift<KC>(L, mu, tk, dg);
       tk = dt;
-      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, h, dt, h, vk);
+      if constexpr (JAC) wide_kick_jacobi<G, GR>(L, wk, jc, kg, dt);
+      else wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, h, dt, h, vk);
     }
   } else {
     double ta = L.first ? 0.0 : h;
     double ti = L.first ? h : dt;
     for (int s = 0; s < n_steps; ++s) {
-      wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, ta, ti, h, vk);
+      if constexpr (JAC) wide_kick_jacobi<G, GR>(L, wk, jc, kg, ti);
+      else wide_kick<G, GR, STORAGE>(L, wk, inv_m0, kg, ta, ti, h, vk);
       ta = h;
       ti = dt;
-      wide_drift<KC>(L, dt, dg);
+      wide_drift<KC>(L, mu, dt, dg);
     }
   }
   wide_flags<G>(p, L, dg, lane);
@@ -373,7 +467,7 @@ __device__ __forceinline__ void wide_store(const StepParams& p, const WideLane& 
   wide_put<STORAGE>(st + 3 * r3 + ns, L.cv);
 }
 
-template <int G, bool GR, int SCHEME, int KC, int STORAGE>
+template <int G, bool GR, int SCHEME, int KC, int STORAGE, bool JAC>
 __device__ __forceinline__ void wide_group(const StepParams& p, int w, double* block, int lane) {
   const int slot = wide_slot<STORAGE>(w, lane), c = wide_comp(lane), ns = p.ns;
   double* st = p.st + (size_t)c * ns + slot;
@@ -389,13 +483,13 @@ __device__ __forceinline__ void wide_group(const StepParams& p, int w, double* b
   L.sys = p.slot_sys[slot];
   L.pl = p.slot_pl[slot];
   L.first = L.sys >= 0 ? p.synced[L.sys] : 1;
-  wide_steps<G, GR, SCHEME, KC, STORAGE>(p, L, block, lane);
+  wide_steps<G, GR, SCHEME, KC, STORAGE, JAC>(p, L, block, lane);
   wide_store<STORAGE>(p, L, slot, c, lane);
 }
 
 // The persistent step kernel of this form, defined and instantiated in
 // wh_wide_step.hip.  Up to four wavefronts per workgroup.
-template <bool GR, int SCHEME, int KC, int STORAGE>
+template <bool GR, int SCHEME, int KC, int STORAGE, bool JAC = false>
 __global__ __launch_bounds__(256) void k_step_wide(StepParams p);
 
 }  // namespace wh

@@ -67,7 +67,7 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
         const double tau = k > 0 ? p.sc[k] * dt : (first_synced && s == 0 ? c1dt : 2.0 * c1dt);
         const double tb = p.sd[k] * dt;
         put_state();
-        const double X = wide_drift<0>(L, tau, dg);
+        const double X = wide_drift<0>(L, L.m0, tau, dg);
         wide_kick<G, false>(L, wk, inv_m0, 0.0, 0.5 * tb, tb, 0.5 * tb, vk);
         put_rest(X);
       }
@@ -79,13 +79,13 @@ __device__ __forceinline__ void wide_record(const StepParams& p, const double* c
       wide_kick<G, GR>(L, wk, inv_m0, kg, ta, ti, h, vk);
       ta = h;
       ti = dt;
-      put_rest(wide_drift<0>(L, dt, dg));
+      put_rest(wide_drift<0>(L, L.m0, dt, dg));
     }
   } else {
     double tk = first_synced ? h : dt;
     for (int s = 0; s < n_rec; ++s) {
       put_state();
-      const double X = wide_drift<0>(L, tk, dg);
+      const double X = wide_drift<0>(L, L.m0, tk, dg);
       tk = dt;
       wide_kick<G, GR>(L, wk, inv_m0, kg, h, dt, h, vk);
       put_rest(X);

@@ -5,7 +5,7 @@
 
 namespace wh {
 
-template <bool GR, int SCHEME, int KC, int STORAGE>
+template <bool GR, int SCHEME, int KC, int STORAGE, bool JAC>
 __global__ __launch_bounds__(256) void k_step_wide(StepParams p) {
   __shared__ double lds[4 * WIDE_LDS];
   const int lane = threadIdx.x & 63, wb = threadIdx.x >> 6;
@@ -13,16 +13,16 @@ __global__ __launch_bounds__(256) void k_step_wide(StepParams p) {
   // wavefront of the launch, then of the packing (4 per wave of 64 slots, 2
   // per wave of the split packing)
   const int k = (int)(blockIdx.x * (blockDim.x >> 6)) + wb;
-  if (STORAGE == 1) {
-    if (k < 2 * p.w8) wide_group<8, GR, SCHEME, KC, 1>(p, k, block, lane);
+  if constexpr (STORAGE == 1) {
+    if (k < 2 * p.w8) wide_group<8, GR, SCHEME, KC, 1, false>(p, k, block, lane);
     return;
   }
   const int w = 4 * p.wave0 + k;
   if (w >= 4 * p.w8) return;
-  if (w < 4 * p.w1) wide_group<1, GR, SCHEME, KC, 0>(p, w, block, lane);
-  else if (w < 4 * p.w2) wide_group<2, GR, SCHEME, KC, 0>(p, w, block, lane);
-  else if (w < 4 * p.w4) wide_group<4, GR, SCHEME, KC, 0>(p, w, block, lane);
-  else wide_group<8, GR, SCHEME, KC, 0>(p, w, block, lane);
+  if (w < 4 * p.w1) wide_group<1, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
+  else if (w < 4 * p.w2) wide_group<2, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
+  else if (w < 4 * p.w4) wide_group<4, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
+  else wide_group<8, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
 }
 
 #define WH_WIDE(STORAGE)                                                     \
@@ -38,5 +38,11 @@ __global__ __launch_bounds__(256) void k_step_wide(StepParams p) {
 WH_WIDE(0);
 WH_WIDE(1);
 #undef WH_WIDE
+template __global__ void k_step_wide<false, WH_DKD, 0, 0, true>(StepParams);
+template __global__ void k_step_wide<true, WH_DKD, 0, 0, true>(StepParams);
+template __global__ void k_step_wide<false, WH_KDK, 0, 0, true>(StepParams);
+template __global__ void k_step_wide<true, WH_KDK, 0, 0, true>(StepParams);
+template __global__ void k_step_wide<false, SCHEME_SABA, 0, 0, true>(StepParams);
+template __global__ void k_step_wide<true, SCHEME_SABA, 0, 0, true>(StepParams);
 
 }  // namespace wh

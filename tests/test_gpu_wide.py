@@ -43,6 +43,18 @@ def test_small_batch_is_bitwise_the_large_one(packing, scheme, gr_c, counts, S, 
         assert np.array_equal(a, b[:S])
 
 
+# and in Jacobi coordinates, whose scans cross the rows of a group
+@pytest.mark.parametrize("scheme,gr_c", [("dkd", 0.0), ("kdk", 40.0), ("saba3", 40.0)])
+@pytest.mark.parametrize("packing", ["pow2", "g8"])
+@pytest.mark.parametrize("S,lo,hi", [(1, 8, 8), (3, 5, 7), (9, 3, 4), (33, 2, 2), (65, 1, 1)])
+def test_small_jacobi_batch_is_bitwise_the_large_one(packing, scheme, gr_c, S, lo, hi):
+    s = inputs.make_systems(S, 34, n_planets=None, n_range=(lo, hi), dt_mode="u15_30")
+    kw = dict(packing=packing, scheme=scheme, gr_c=gr_c, coords="jacobi")
+    big = {8: 4104, 4: 8200, 2: 16400, 1: 32800}[8 if hi > 4 or packing != "pow2" else 4 if hi > 2 else hi] * 2
+    for a, b in zip(final(s, **kw), final(tiled(s, big), **kw)):
+        assert np.array_equal(a, b[:S])
+
+
 def test_trouble_stays_in_its_system():
     """Unbound, non-finite and coincident planets: flags and states as in the
     large batch, the neighbours' among them."""
