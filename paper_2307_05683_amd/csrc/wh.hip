@@ -441,6 +441,27 @@ __global__ __launch_bounds__(256) void k_step(StepParams p) {
   else step_group<8, GR, SCHEME, EXCH, JAC, KC>(p, slot, lane);
 }
 
+// The same over even shares of the launch (EvenShare, wh_host.h): wavefront k
+// runs bin k's slice, piece after piece; lane i works piece i out.
+template <bool GR, int SCHEME> __global__ __launch_bounds__(256) void k_step_even(StepParams p, EvenShare e) {
+  __shared__ int2 pieces[4][EVEN_PIECES];
+  const int lane = threadIdx.x & 63, wb = threadIdx.x >> 6;
+  const int bin = (int)blockIdx.x * 4 + wb;
+  if (bin >= e.bins) return;
+  int2 mine{0, 0};
+  even_piece(e, bin, lane, mine.x, mine.y);
+  pieces[wb][lane] = mine;
+  wave_lds_fence();
+  for (unsigned long long todo = __ballot(mine.y > 0); todo; todo &= todo - 1) {
+    const int2 piece = pieces[wb][__builtin_ctzll(todo)];
+    const int wave = piece.x, slot = wave * 64 + lane;
+    p.n_steps = piece.y;
+    if (wave < p.w1) step_group<1, GR, SCHEME, 1, false>(p, slot, lane);
+    else if (wave < p.w2) step_group<2, GR, SCHEME, 1, false>(p, slot, lane);
+    else if (wave < p.w4) step_group<4, GR, SCHEME, 1, false>(p, slot, lane);
+    else step_group<8, GR, SCHEME, 1, false>(p, slot, lane);
+  }
+}
 
 // ---------------------------------------------------------------------------
 // The mixed packing (WH_PACK_MIXED): waves [wm, w8) hold two systems per
@@ -2850,6 +2871,7 @@ struct wh_ctx {
   int* plan_wave = nullptr;
   int* plan_steps = nullptr;
   int plan_slots = 0;   // wavefronts the GPU holds at the kernel's occupancy
+  int simds = 0;        // of the GPU
   int wide_waves = 0;   // wavefronts of the step with four lanes per planet (0: not used)
   int wide_block = 1;   // and of its workgroups
 };
@@ -3009,14 +3031,15 @@ void launch_wide(const wh_ctx* c, const StepParams& p, hipStream_t st) {
 // 1.08, 6144 both 1.08.
 wh_status choose_wide(wh_ctx* c) {
   c->wide_waves = 0;
-  if (c->P.pair || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP) return WH_OK;
   int dev = 0, ncu = 0;
   wh_status st;
   if ((st = hip_check(hipGetDevice(&dev), "hipGetDevice")) ||
       (st = hip_check(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev), "CU count")))
     return st;
+  c->simds = 4 * ncu;   // four SIMDs per compute unit
+  if (c->P.pair || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP) return WH_OK;
   const int64_t waves = c->P.ns / (c->P.split ? 2 * WIDE_SLOTS : WIDE_SLOTS);
-  if (waves > (int64_t)4 * ncu) return WH_OK;   // four SIMDs per compute unit
+  if (waves > c->simds) return WH_OK;
   c->wide_waves = (int)waves;
   // one-wave workgroups go to compute units in turn; beyond one per unit,
   // four-wave workgroups give each wavefront a SIMD of its own
@@ -3024,9 +3047,50 @@ wh_status choose_wide(wh_ctx* c) {
   return WH_OK;
 }
 
+// Even shares of a launch over the whole packing, for DHC with the paper's
+// Kepler counts in the one-planet packings.  W waves on so many SIMDs put
+// ceil(W / SIMDs) on the busiest, whose time per step (eight-planet waves, us)
+// is 1.04, 1.87, 2.67 and 3.66 for one to four.  With a bin per SIMD an average
+// load of L eight-planet waves takes 1.04 L, with two 0.94 L, and each slice
+// some 8 us.  At 300 steps: L = 1.22 (10000 systems) 1.91 -> 1.45 us per step, 1.5
+// 1.87 -> 1.64, 1.71 1.87 -> 1.78, 2.0 1.96 -> 2.10; two bins per SIMD: 2.44
+// (20000) 2.67 -> 2.49, 3.06 (40011 systems of one to eight) 3.55 -> 3.21, 3.66
+// 3.66 -> 3.67; at 1000 steps L = 1.2 (9900 systems) 1.75 -> 1.20.  Beyond four
+// waves per SIMD the hardware's own dispatch evens the load out.
+bool choose_even(const wh_ctx* c, int n_steps, EvenShare& e) {
+  if (c->P.pair || c->P.split || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP ||
+      c->cfg.coords != WH_COORDS_DHC || c->cfg.kepler_counts != 0)
+    return false;
+  const int busiest = (c->P.nwaves + c->simds - 1) / c->simds;
+  if (busiest < 2 || busiest > 4) return false;
+  const int w[5] = {0, c->P.w1, c->P.w2, c->P.w4, c->P.w8};
+  for (int g = 0; g < 5; ++g) e.first[g] = w[g];
+  for (int g = 0; g < 4; ++g) e.cost[g] = w[g + 1] > w[g] ? (int)wave_step_cost(c->P, c->cfg.gr_c > 0, w[g]) : 1;
+  const double load = even_total(e) / ((double)c->simds * *std::max_element(e.cost, e.cost + 4));
+  if (load > (busiest == 2 ? 1.65 : busiest == 3 ? 2.6 : 3.4)) return false;
+  e.bins = busiest == 2 ? c->simds : 2 * c->simds;
+  e.steps = n_steps;
+  e.slices = even_slices(e, 6);
+  const int kicks = c->cfg.scheme >= WH_SABA2 ? c->cfg.scheme : 1;   // per step
+  return e.slices > 0 && (int64_t)n_steps * kicks >= 64 * e.slices;
+}
+void launch_even(const wh_ctx* c, const StepParams& p, EvenShare e, hipStream_t st) {
+  const bool gr = c->cfg.gr_c > 0, dkd = c->cfg.scheme == WH_DKD;
+  const dim3 grid((e.bins + 3) / 4), block(256);
+  for (e.slice = 0; e.slice < e.slices; ++e.slice) {
+    if (c->cfg.scheme >= WH_SABA2) hipLaunchKernelGGL((k_step_even<false, SCHEME_SABA>), grid, block, 0, st, p, e);
+    else if (dkd && gr) hipLaunchKernelGGL((k_step_even<true, WH_DKD>), grid, block, 0, st, p, e);
+    else if (dkd) hipLaunchKernelGGL((k_step_even<false, WH_DKD>), grid, block, 0, st, p, e);
+    else if (gr) hipLaunchKernelGGL((k_step_even<true, WH_KDK>), grid, block, 0, st, p, e);
+    else hipLaunchKernelGGL((k_step_even<false, WH_KDK>), grid, block, 0, st, p, e);
+  }
+}
+
 void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
   StepParams p = step_params(c, n_steps);
+  EvenShare e{};
   if (c->wide_waves > 0) launch_wide(c, p, st);
+  else if (choose_even(c, n_steps, e)) launch_even(c, p, e, st);
   else launch_step_kernel(c, p, c->P.nwaves, st);
 }
 

@@ -529,4 +529,105 @@ inline void plan_windows(const std::vector<double>& cost, int R, int slots, int 
   }
 }
 
+// Even shares of a launch (McNaughton's wrap-around rule).  The one-planet
+// packing's waves of one group size cost the same, so laying all waves end to
+// end by cost and cutting the line into `bins` equal parts gives every bin the
+// same work.  A cut wave runs its first steps at the start of the lower bin
+// and the others at the end of the upper one; `slices` launches cut the bins'
+// time, and where no wave is longer than a bin less a slice (even_slices), one
+// of those cuts lies between the two parts.  Whole numbers below 2^52 in
+// double precision: exact.
+#ifdef __HIPCC__
+#define WH_HD __host__ __device__
+#else
+#define WH_HD
+#endif
+constexpr int EVEN_PIECES = 64;    // pieces of a bin, at most
+struct EvenShare {
+  int first[5];        // wave ranges of the four group sizes
+  int cost[4];         // of a step
+  int bins, slices, slice;
+  int steps;           // of every wave
+};
+WH_HD inline double even_div(double a, double b) { return __builtin_floor(a / b); }
+// Place on the line where wave w starts, and the cost of its step.
+WH_HD inline double even_start(const EvenShare& e, int w, int& cost) {
+  double a = 0.0;
+  cost = e.cost[3];
+#if defined(__clang__)
+#pragma unroll
+#endif
+  for (int g = 0; g < 4; ++g) {
+    const int n = e.first[g + 1] - e.first[g], k = w - e.first[g];
+    a += (double)(k < 0 ? 0 : k < n ? k : n) * e.cost[g];
+    if (k >= 0 && k < n) cost = e.cost[g];
+  }
+  return a;
+}
+WH_HD inline double even_total(const EvenShare& e) {
+  int c;
+  return even_start(e, e.first[4], c);
+}
+// Wave at place x (the number of waves at the line's end).
+WH_HD inline int even_wave_at(const EvenShare& e, double x) {
+  double a = 0.0;
+  int w = e.first[4];
+  bool found = false;
+#if defined(__clang__)
+#pragma unroll
+#endif
+  for (int g = 0; g < 4; ++g) {
+    const double len = (double)(e.first[g + 1] - e.first[g]) * e.cost[g];
+    if (!found && x < a + len) {
+      w = e.first[g] + (int)even_div(x - a, e.cost[g]);
+      found = true;
+    }
+    a += len;
+  }
+  return w;
+}
+// Piece i of a bin, in the order they run: the first steps of the wave cut at
+// the bin's end, the whole waves, the last steps of the wave cut at its start.
+// Its wave, and how many of its steps fall into the slice; false: there is no
+// such piece.
+WH_HD inline bool even_piece(const EvenShare& e, int bin, int i, int& wave, int& steps) {
+  const double C = even_total(e), R = e.steps;
+  const double x0 = even_div(bin * C, e.bins), x1 = even_div((bin + 1) * C, e.bins);
+  const int tail = even_wave_at(e, x0), head = even_wave_at(e, x1);
+  int ct, ch, cost, dummy;
+  const double off_t = x0 - even_start(e, tail, ct), off_h = x1 - even_start(e, head, ch);
+  const double head_steps = even_div(off_h * R, ch), tail_steps = off_t > 0.0 ? R - even_div(off_t * R, ct) : 0.0;
+  const int from = tail + (off_t > 0.0 ? 1 : 0), whole = head - from;
+  if (i > whole + 1) return false;
+  wave = i == 0 ? head : i <= whole ? from + i - 1 : tail;
+  const double n = i == 0 ? head_steps : i <= whole ? R : tail_steps;
+  steps = 0;
+  if (!(n > 0.0)) return true;
+  const double start = even_start(e, wave, cost), line0 = even_start(e, from, dummy);
+  const double at = i == 0 ? 0.0 : head_steps * ch + R * ((i <= whole ? start : even_start(e, head, dummy)) - line0);
+  const double T = C * R, m = (double)e.bins * e.slices;
+  double done = even_div(even_div(e.slice * T, m) - at, cost), end = even_div(even_div((e.slice + 1) * T, m) - at, cost);
+  done = done < 0.0 ? 0.0 : done < n ? done : n;
+  end = e.slice + 1 == e.slices ? n : end < 0.0 ? 0.0 : end < n ? end : n;
+  steps = (int)(end - done);
+  return true;
+}
+// Slices such that one of their cuts lies between the two parts of any cut
+// wave, whose time is at most a bin's less a slice's (and four steps, for the
+// roundings); 0 if that would take more than `most` or more pieces than there
+// is room for.
+inline int even_slices(const EvenShare& e, int most) {
+  const double bin = even_total(e) / e.bins;
+  double c = 0.0, least = 1.0e300;
+  for (int g = 0; g < 4; ++g)
+    if (e.first[g + 1] > e.first[g]) {
+      c = std::max(c, (double)e.cost[g]);
+      least = std::min(least, (double)e.cost[g]);
+    }
+  const double room = bin * e.steps - c * (e.steps + 4.0);
+  if (room <= 0.0 || bin / least + 4.0 > EVEN_PIECES || even_total(e) * e.steps * e.bins > 4.0e15) return 0;
+  const double m = std::ceil(bin * e.steps / room);
+  return m <= most ? (int)std::max(m, 2.0) : 0;
+}
+
 }  // namespace wh_host
