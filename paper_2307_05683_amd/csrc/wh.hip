@@ -441,28 +441,6 @@ __global__ __launch_bounds__(256) void k_step(StepParams p) {
   else step_group<8, GR, SCHEME, EXCH, JAC, KC>(p, slot, lane);
 }
 
-// The same over even shares of the launch (EvenShare, wh_host.h): wavefront k
-// runs bin k's slice, piece after piece; lane i works piece i out.
-template <bool GR, int SCHEME> __global__ __launch_bounds__(256) void k_step_even(StepParams p, EvenShare e) {
-  __shared__ int2 pieces[4][EVEN_PIECES];
-  const int lane = threadIdx.x & 63, wb = threadIdx.x >> 6;
-  const int bin = (int)blockIdx.x * 4 + wb;
-  if (bin >= e.bins) return;
-  int2 mine{0, 0};
-  even_piece(e, bin, lane, mine.x, mine.y);
-  pieces[wb][lane] = mine;
-  wave_lds_fence();
-  for (unsigned long long todo = __ballot(mine.y > 0); todo; todo &= todo - 1) {
-    const int2 piece = pieces[wb][__builtin_ctzll(todo)];
-    const int wave = piece.x, slot = wave * 64 + lane;
-    p.n_steps = piece.y;
-    if (wave < p.w1) step_group<1, GR, SCHEME, 1, false>(p, slot, lane);
-    else if (wave < p.w2) step_group<2, GR, SCHEME, 1, false>(p, slot, lane);
-    else if (wave < p.w4) step_group<4, GR, SCHEME, 1, false>(p, slot, lane);
-    else step_group<8, GR, SCHEME, 1, false>(p, slot, lane);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // The mixed packing (WH_PACK_MIXED): waves [wm, w8) hold two systems per
 // 8-lane group (ExchMixed); the other waves are those of the one-planet
@@ -502,6 +480,12 @@ __device__ __forceinline__ void step_lane_mixed(const StepParams& p, Lane& L, in
   }
 }
 
+template <bool GR, int SCHEME> __device__ void step_group_mixed(const StepParams& p, int slot, int lane) {
+  Lane L = load_lane(p, slot);
+  step_lane_mixed<GR, SCHEME>(p, L, lane);
+  store_lane(p, slot, L);
+}
+
 template <bool GR, int SCHEME>
 __global__ __launch_bounds__(256) void k_step_mixed(StepParams p) {
   const int lane = threadIdx.x & 63;
@@ -512,10 +496,30 @@ __global__ __launch_bounds__(256) void k_step_mixed(StepParams p) {
   else if (wave < p.w2) step_group<2, GR, SCHEME, 1, false>(p, slot, lane);
   else if (wave < p.w4) step_group<4, GR, SCHEME, 1, false>(p, slot, lane);
   else if (wave < p.wm) step_group<8, GR, SCHEME, 1, false>(p, slot, lane);
-  else {
-    Lane L = load_lane(p, slot);
-    step_lane_mixed<GR, SCHEME>(p, L, lane);
-    store_lane(p, slot, L);
+  else step_group_mixed<GR, SCHEME>(p, slot, lane);
+}
+
+// k_step and k_step_mixed over even shares of the launch (EvenShare, wh_host.h):
+// wavefront k runs bin k's slice, piece after piece; lane i works piece i out.
+template <bool GR, int SCHEME, bool MIXED = false>
+__global__ __launch_bounds__(256) void k_step_even(StepParams p, EvenShare e) {
+  __shared__ int2 pieces[4][EVEN_PIECES];
+  const int lane = threadIdx.x & 63, wb = threadIdx.x >> 6;
+  const int bin = (int)blockIdx.x * 4 + wb;
+  if (bin >= e.bins) return;
+  int2 mine{0, 0};
+  even_piece(e, bin, lane, mine.x, mine.y);
+  pieces[wb][lane] = mine;
+  wave_lds_fence();
+  for (unsigned long long todo = __ballot(mine.y > 0); todo; todo &= todo - 1) {
+    const int2 piece = pieces[wb][__builtin_ctzll(todo)];
+    const int wave = piece.x, slot = wave * 64 + lane;
+    p.n_steps = piece.y;
+    if (wave < p.w1) step_group<1, GR, SCHEME, 1, false>(p, slot, lane);
+    else if (wave < p.w2) step_group<2, GR, SCHEME, 1, false>(p, slot, lane);
+    else if (wave < p.w4) step_group<4, GR, SCHEME, 1, false>(p, slot, lane);
+    else if (!MIXED || wave < p.wm) step_group<8, GR, SCHEME, 1, false>(p, slot, lane);
+    else if constexpr (MIXED) step_group_mixed<GR, SCHEME>(p, slot, lane);
   }
 }
 
@@ -2872,6 +2876,7 @@ struct wh_ctx {
   int* plan_steps = nullptr;
   int plan_slots = 0;   // wavefronts the GPU holds at the kernel's occupancy
   int simds = 0;        // of the GPU
+  EvenShare even{};     // even shares of a balanced chunk (slices = 0: none)
   int wide_waves = 0;   // wavefronts of the step with four lanes per planet (0: not used)
   int wide_block = 1;   // and of its workgroups
 };
@@ -3047,10 +3052,26 @@ wh_status choose_wide(wh_ctx* c) {
   return WH_OK;
 }
 
-// Even shares of a launch over the whole packing, for DHC with the paper's
-// Kepler counts in the one-planet packings.  W waves on so many SIMDs put
-// ceil(W / SIMDs) on the busiest, whose time per step (eight-planet waves, us)
-// is 1.04, 1.87, 2.67 and 3.66 for one to four.  With a bin per SIMD an average
+// Even shares of n_steps over bins of the launch, for DHC with the paper's Kepler
+// counts in the one-planet and mixed packings; false if there is no such cut.
+// A slice takes some 8 us beyond its steps, which 64 steps outweigh.
+bool even_form(const wh_ctx* c, int bins, int n_steps, EvenShare& e) {
+  const Packing& P = c->P;
+  if (P.pair || P.split || P.serial || c->exchange != WH_EXCH_DPP || c->cfg.coords != WH_COORDS_DHC ||
+      c->cfg.kepler_counts != 0)
+    return false;
+  const int w[6] = {0, P.w1, P.w2, P.w4, P.mixed ? P.wm : P.w8, P.w8};
+  for (int g = 0; g < 6; ++g) e.first[g] = w[g];
+  for (int g = 0; g < 5; ++g) e.cost[g] = w[g + 1] > w[g] ? (int)wave_step_cost(P, c->cfg.gr_c > 0, w[g]) : 1;
+  e.bins = bins;
+  e.steps = n_steps;
+  const int64_t kicks = (int64_t)n_steps * (c->cfg.scheme >= WH_SABA2 ? c->cfg.scheme : 1);
+  e.slices = even_slices(e, (int)std::min<int64_t>(kicks / 64, 32));
+  return e.slices > 0;
+}
+// When an unbalanced launch takes even shares.  W waves put ceil(W / SIMDs) on
+// the busiest SIMD, whose time per step (eight-planet waves, us) is 1.04, 1.87,
+// 2.67 and 3.66 for one to four.  With a bin per SIMD an average
 // load of L eight-planet waves takes 1.04 L, with two 0.94 L, and each slice
 // some 8 us.  At 300 steps: L = 1.22 (10000 systems) 1.91 -> 1.45 us per step, 1.5
 // 1.87 -> 1.64, 1.71 1.87 -> 1.78, 2.0 1.96 -> 2.10; two bins per SIMD: 2.44
@@ -3058,27 +3079,21 @@ wh_status choose_wide(wh_ctx* c) {
 // 3.66 -> 3.67; at 1000 steps L = 1.2 (9900 systems) 1.75 -> 1.20.  Beyond four
 // waves per SIMD the hardware's own dispatch evens the load out.
 bool choose_even(const wh_ctx* c, int n_steps, EvenShare& e) {
-  if (c->P.pair || c->P.split || c->P.serial || c->P.mixed || c->exchange != WH_EXCH_DPP ||
-      c->cfg.coords != WH_COORDS_DHC || c->cfg.kepler_counts != 0)
-    return false;
   const int busiest = (c->P.nwaves + c->simds - 1) / c->simds;
-  if (busiest < 2 || busiest > 4) return false;
-  const int w[5] = {0, c->P.w1, c->P.w2, c->P.w4, c->P.w8};
-  for (int g = 0; g < 5; ++g) e.first[g] = w[g];
-  for (int g = 0; g < 4; ++g) e.cost[g] = w[g + 1] > w[g] ? (int)wave_step_cost(c->P, c->cfg.gr_c > 0, w[g]) : 1;
-  const double load = even_total(e) / ((double)c->simds * *std::max_element(e.cost, e.cost + 4));
-  if (load > (busiest == 2 ? 1.65 : busiest == 3 ? 2.6 : 3.4)) return false;
-  e.bins = busiest == 2 ? c->simds : 2 * c->simds;
-  e.steps = n_steps;
-  e.slices = even_slices(e, 6);
-  const int kicks = c->cfg.scheme >= WH_SABA2 ? c->cfg.scheme : 1;   // per step
-  return e.slices > 0 && (int64_t)n_steps * kicks >= 64 * e.slices;
+  if (busiest < 2 || busiest > 4 || !even_form(c, busiest == 2 ? c->simds : 2 * c->simds, n_steps, e)) return false;
+  const double load = even_total(e) / ((double)c->simds * *std::max_element(e.cost, e.cost + 5));
+  return load <= (busiest == 2 ? 1.65 : busiest == 3 ? 2.6 : 3.4);
 }
 void launch_even(const wh_ctx* c, const StepParams& p, EvenShare e, hipStream_t st) {
   const bool gr = c->cfg.gr_c > 0, dkd = c->cfg.scheme == WH_DKD;
   const dim3 grid((e.bins + 3) / 4), block(256);
   for (e.slice = 0; e.slice < e.slices; ++e.slice) {
-    if (c->cfg.scheme >= WH_SABA2) hipLaunchKernelGGL((k_step_even<false, SCHEME_SABA>), grid, block, 0, st, p, e);
+    if (c->P.mixed) {
+      if (dkd && gr) hipLaunchKernelGGL((k_step_even<true, WH_DKD, true>), grid, block, 0, st, p, e);
+      else if (dkd) hipLaunchKernelGGL((k_step_even<false, WH_DKD, true>), grid, block, 0, st, p, e);
+      else if (gr) hipLaunchKernelGGL((k_step_even<true, WH_KDK, true>), grid, block, 0, st, p, e);
+      else hipLaunchKernelGGL((k_step_even<false, WH_KDK, true>), grid, block, 0, st, p, e);
+    } else if (c->cfg.scheme >= WH_SABA2) hipLaunchKernelGGL((k_step_even<false, SCHEME_SABA>), grid, block, 0, st, p, e);
     else if (dkd && gr) hipLaunchKernelGGL((k_step_even<true, WH_DKD>), grid, block, 0, st, p, e);
     else if (dkd) hipLaunchKernelGGL((k_step_even<false, WH_DKD>), grid, block, 0, st, p, e);
     else if (gr) hipLaunchKernelGGL((k_step_even<true, WH_KDK>), grid, block, 0, st, p, e);
@@ -3103,6 +3118,7 @@ void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
 wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
   c->plan_off.clear();
   c->plan_slots = 0;
+  c->even = EvenShare{};
   hw.clear();
   hs.clear();
   if (c->cfg.balance != 1 || c->P.serial || c->wide_waves > 0) return WH_OK;
@@ -3124,6 +3140,10 @@ wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
   if (k < 1) return WH_OK;
   const int slots = k * simds;
   if (W <= slots || W > 16 * slots) return WH_OK;
+  if (even_form(c, slots, c->chunk, c->even)) {
+    c->plan_slots = slots;
+    return WH_OK;
+  }
   std::vector<double> cost(W);
   for (int w = 0; w < W; ++w) cost[w] = wave_step_cost(c->P, c->cfg.gr_c > 0, w);
   plan_windows(cost, c->chunk, slots, PLAN_Q, hw, hs, c->plan_off);
@@ -3135,6 +3155,10 @@ wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
 // One chunk of c->chunk steps for every wave: the balanced windows, or one
 // launch.
 void launch_chunk(const wh_ctx* c, hipStream_t st) {
+  if (c->even.slices > 0) {
+    launch_even(c, step_params(c, c->chunk), c->even, st);
+    return;
+  }
   if (c->plan_off.size() < 2) {
     launch_step(c, c->chunk, st);
     return;
@@ -3617,6 +3641,7 @@ wh_status wh_restore_state(wh_ctx* c, const void* src, size_t bytes, hipStream_t
 int32_t wh_launch_windows(const wh_ctx* c, int32_t* slots) {
   if (!c) return -1;
   if (slots) *slots = c->plan_slots;
+  if (c->even.slices > 0) return c->even.slices;
   return c->plan_off.size() < 2 ? 1 : (int32_t)c->plan_off.size() - 1;
 }
 

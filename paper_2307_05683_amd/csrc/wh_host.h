@@ -530,7 +530,7 @@ inline void plan_windows(const std::vector<double>& cost, int R, int slots, int 
 }
 
 // Even shares of a launch (McNaughton's wrap-around rule).  The one-planet
-// packing's waves of one group size cost the same, so laying all waves end to
+// packings' waves of one group size cost the same, so laying all waves end to
 // end by cost and cutting the line into `bins` equal parts gives every bin the
 // same work.  A cut wave runs its first steps at the start of the lower bin
 // and the others at the end of the upper one; `slices` launches cut the bins'
@@ -544,8 +544,8 @@ inline void plan_windows(const std::vector<double>& cost, int R, int slots, int 
 #endif
 constexpr int EVEN_PIECES = 64;    // pieces of a bin, at most
 struct EvenShare {
-  int first[5];        // wave ranges of the four group sizes
-  int cost[4];         // of a step
+  int first[6];        // wave ranges of the four group sizes and the shared 8-lane groups
+  int cost[5];         // of a step
   int bins, slices, slice;
   int steps;           // of every wave
 };
@@ -553,11 +553,11 @@ WH_HD inline double even_div(double a, double b) { return __builtin_floor(a / b)
 // Place on the line where wave w starts, and the cost of its step.
 WH_HD inline double even_start(const EvenShare& e, int w, int& cost) {
   double a = 0.0;
-  cost = e.cost[3];
+  cost = e.cost[4];
 #if defined(__clang__)
 #pragma unroll
 #endif
-  for (int g = 0; g < 4; ++g) {
+  for (int g = 0; g < 5; ++g) {
     const int n = e.first[g + 1] - e.first[g], k = w - e.first[g];
     a += (double)(k < 0 ? 0 : k < n ? k : n) * e.cost[g];
     if (k >= 0 && k < n) cost = e.cost[g];
@@ -566,17 +566,17 @@ WH_HD inline double even_start(const EvenShare& e, int w, int& cost) {
 }
 WH_HD inline double even_total(const EvenShare& e) {
   int c;
-  return even_start(e, e.first[4], c);
+  return even_start(e, e.first[5], c);
 }
 // Wave at place x (the number of waves at the line's end).
 WH_HD inline int even_wave_at(const EvenShare& e, double x) {
   double a = 0.0;
-  int w = e.first[4];
+  int w = e.first[5];
   bool found = false;
 #if defined(__clang__)
 #pragma unroll
 #endif
-  for (int g = 0; g < 4; ++g) {
+  for (int g = 0; g < 5; ++g) {
     const double len = (double)(e.first[g + 1] - e.first[g]) * e.cost[g];
     if (!found && x < a + len) {
       w = e.first[g] + (int)even_div(x - a, e.cost[g]);
@@ -619,7 +619,7 @@ WH_HD inline bool even_piece(const EvenShare& e, int bin, int i, int& wave, int&
 inline int even_slices(const EvenShare& e, int most) {
   const double bin = even_total(e) / e.bins;
   double c = 0.0, least = 1.0e300;
-  for (int g = 0; g < 4; ++g)
+  for (int g = 0; g < 5; ++g)
     if (e.first[g + 1] > e.first[g]) {
       c = std::max(c, (double)e.cost[g]);
       least = std::min(least, (double)e.cost[g]);

@@ -10,7 +10,7 @@ using namespace wh_host;
 
 int main() {
   std::mt19937 r(1);
-  const int costs[2][4] = {{316, 331, 378, 478}, {330, 367, 416, 526}}, bins[] = {1024, 2048, 7, 64};
+  const int costs[2][5] = {{316, 331, 378, 478, 543}, {330, 367, 416, 526, 598}}, bins[] = {1024, 2048, 7, 64};
   const int steps[] = {64, 100, 300, 1000, 4096, 1000000};
   int used = 0, by_slices[7] = {0};
   for (int t = 0; t < 1500; ++t) {
@@ -18,11 +18,11 @@ int main() {
     const int c = r() % 2;
     e.bins = bins[r() % 4];
     e.steps = steps[r() % 6];
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < 5; ++g) {
       e.cost[g] = costs[c][g];
-      e.first[g + 1] = e.first[g] + (r() % 3 == 0 ? 0 : (int)(r() % (3 * e.bins / 2)));
+      e.first[g + 1] = e.first[g] + (r() % 3 == 0 ? 0 : (int)(r() % (5 * e.bins / 4)));
     }
-    const int W = e.first[4];
+    const int W = e.first[5];
     if (W == 0 || (e.slices = even_slices(e, 6)) == 0) continue;
     ++used;
     ++by_slices[e.slices];
@@ -40,11 +40,11 @@ int main() {
           if (seen[w]) return std::printf("wave %d twice in slice %d of %d\n", w, e.slice, e.slices), 1;
           seen[w] = 1;
           done[w] += s;
-          weight += (double)s * e.cost[w < e.first[1] ? 0 : w < e.first[2] ? 1 : w < e.first[3] ? 2 : 3];
+          weight += (double)s * e.cost[w < e.first[1] ? 0 : w < e.first[2] ? 1 : w < e.first[3] ? 2 : w < e.first[4] ? 3 : 4];
         }
         // a bin's ends are rounded to whole units of a step's cost, its cuts
         // to whole steps
-        if (weight > share + e.steps + 4 * 526) return std::printf("slice %g of %g\n", weight, share), 1;
+        if (weight > share + e.steps + 4 * 598) return std::printf("slice %g of %g\n", weight, share), 1;
       }
     }
     for (int w = 0; w < W; ++w)
