@@ -474,8 +474,11 @@ inline TapeLayout tape_layout(int ns, int64_t n_steps, int64_t every, int units)
 // group size, scaled to the 8-lane group's VALU instructions per lane-step
 // (1024 one-size wavefronts: 0.662 / 0.692 / 0.791 of the 8-lane step for
 // 1, 2, 4 lanes without GR, 0.627 / 0.698 / 0.790 with; the instruction
-// counts, 293 / 326 / 372 / 478, had the 4-lane waves 1.6% too cheap).  Two
-// planets per lane: VALU instructions per lane-step.
+// counts, 293 / 326 / 372 / 478, had the 4-lane waves 1.6% too cheap).  Shared
+// groups: the cost that runs the uneven batch (16384 systems of 2 to 8 planets)
+// fastest in even shares: without GR 1.300 us per step at 543, 1.320 at 530 and
+// 1.331 at 570; with GR 1.465 at 626, 1.484 at 612, 1.494 at 598 and 1.480 at
+// 640.  Two planets per lane: VALU instructions per lane-step.
 inline double wave_step_cost(const Packing& P, bool with_gr, int w) {
   const int gr = with_gr ? 1 : 0;
   if (P.split) return 1.0;
@@ -484,7 +487,7 @@ inline double wave_step_cost(const Packing& P, bool with_gr, int w) {
     return t[gr][w < P.w1 ? 0 : w < P.w2 ? 1 : 2];
   }
   static const double t[2][4] = {{316, 331, 378, 478}, {330, 367, 416, 526}};
-  static const double mixed[2] = {543, 598};
+  static const double mixed[2] = {543, 626};
   if (P.mixed && w >= P.wm) return mixed[gr];
   return t[gr][w < P.w1 ? 0 : w < P.w2 ? 1 : w < P.w4 ? 2 : 3];
 }
