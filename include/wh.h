@@ -142,12 +142,14 @@ typedef struct {
   int32_t balance;     /* 1: balanced launch windows.  When the packing has more wavefronts than the GPU
                           can hold at its occupancy, one launch per chunk leaves some SIMDs a wave more
                           than others; instead each chunk of chunk_steps steps runs as a sequence of
-                          launches ("windows") of at most (resident waves per SIMD) x (SIMDs)
-                          wavefronts, each wave given a share of the chunk's steps in inverse proportion
-                          to its per-step cost (group size), so that every SIMD carries about the same
-                          work in every window.  Results are bitwise those of balance = 0 (a launch
-                          boundary only stores and reloads the state).  WH_PACK_SERIAL ignores it.
-                          0: one launch per chunk. */
+                          launches ("windows") in which every SIMD carries about the same work: even
+                          shares of the waves' steps over (resident waves per SIMD) x (SIMDs) wavefronts
+                          (DHC with the DPP exchange and kepler_counts 0 in the POW2, G8 and MIXED
+                          packings), else windows of at most that many wavefronts, each wave given steps
+                          in inverse proportion to its per-step cost (group size).  Results are bitwise
+                          those of balance = 0 (a launch boundary only stores and reloads the state).
+                          WH_PACK_SERIAL ignores it.  0: one launch per chunk, or a few where the busiest
+                          SIMD would run two to four wavefronts and even shares save time. */
   int32_t kepler_counts; /* iteration counts of the step's Kepler solve (Sec. 3.2, App. A): 0 the paper's
                             (2 Halley steps with 4 series terms, then 2 Newton steps with 8); 1 one Halley
                             step with 3 terms, then the same 2 Newton steps -- the cheapest set the envelope
@@ -243,20 +245,21 @@ size_t wh_state_bytes(const wh_ctx* ctx);
 wh_status wh_save_state(wh_ctx* ctx, void* dst, size_t bytes, hipStream_t stream);
 wh_status wh_restore_state(wh_ctx* ctx, const void* src, size_t bytes, hipStream_t stream);
 
-/* Launches per chunk of wh_step_n: 1 without balanced windows (or when the
- * packing fits the GPU's resident wavefronts), else the number of windows;
- * *slots (may be null) receives the wavefronts per window the plan assumed
- * resident (0 without a plan).  -1 for a null context.  Host-only query. */
+/* Launches per chunk of wh_step_n with wh_config.balance = 1: the number of
+ * windows, or 1 without them (or when the packing fits the GPU's resident
+ * wavefronts); *slots (may be null) receives the wavefronts per window the
+ * plan assumed resident (0 without a plan).  -1 for a null context.  Host-only query. */
 int32_t wh_launch_windows(const wh_ctx* ctx, int32_t* slots);
 
 /* ---- reverse mode ------------------------------------------------------
  * Gradients of a loss of the synchronized final state with respect to the
  * initial synchronized state (Q0, V0), the planet masses and the star mass.
  * Usage: wh_init; wh_forward_ckpt(n, K, tape) (advances the context like
- * wh_step_n and stores a checkpoint every K steps in the tape);
+ * wh_step_n, stores a checkpoint every K steps in the tape and records the
+ * last segment on the way);
  * wh_adjoint_n(tape, dL/dQ_T, dL/dV_T) -> dL/dQ_0, dL/dV_0, dL/dm, dL/dm0.
- * The adjoint re-runs each K-step segment from its checkpoint, records the
- * segment's per-step states and converged Kepler anomalies in the tape, and
+ * The adjoint re-runs each earlier K-step segment from its checkpoint,
+ * records the segment's per-step states and converged Kepler anomalies in the tape, and
  * sweeps it backwards with the hand-written transposed Jacobian of every
  * sub-step (the Kepler drift through the implicit function theorem); the
  * tape holds two segment buffers, so that segment k - 1 is recorded while
