@@ -2868,7 +2868,8 @@ struct wh_ctx {
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
-  // balanced launch windows of one chunk (empty: one launch per chunk):
+  // balanced launch windows of one chunk (empty: one launch per chunk, or even
+  // shares):
   // window k covers entries [plan_off[k], plan_off[k + 1]) of the device
   // tables plan_wave / plan_steps
   std::vector<int> plan_off;
@@ -3111,8 +3112,13 @@ void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
 
 // Balanced launch windows for one chunk (wh_config.balance): slots =
 // (resident waves per SIMD at the step kernel's occupancy) x (SIMDs), using at
-// most as many waves per SIMD as the packing has waves for; plan_windows
-// (wh_host.h) cuts the chunk.  No plan (one launch per chunk) when the
+// most as many waves per SIMD as the packing has waves for.  The chunk runs as
+// even shares over the slots where there are any, else plan_windows (wh_host.h)
+// cuts it.  Chunks of 4096 steps, us per step in windows and in shares: 12000
+// systems of eight 1.46 and 1.42, 20000 2.26 and 2.18, 40000 4.36 and 4.30; 20000 systems
+// of two to six in the mixed packing 1.31 and 1.28.  With several waves of
+// shared groups on a SIMD the windows lead: 35000 such systems 2.03 and 2.05,
+// 49152 of one to eight 3.12 and 3.16.  No plan (one launch per chunk) when the
 // packing has no more waves than slots, or more than 16 per slot (the single
 // launch's imbalance is then small), or for the serial layout.
 wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
@@ -3140,10 +3146,11 @@ wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
   if (k < 1) return WH_OK;
   const int slots = k * simds;
   if (W <= slots || W > 16 * slots) return WH_OK;
-  if (even_form(c, slots, c->chunk, c->even)) {
+  if ((k == 1 || !c->P.mixed || c->P.wm == c->P.w8) && even_form(c, slots, c->chunk, c->even)) {
     c->plan_slots = slots;
     return WH_OK;
   }
+  c->even = EvenShare{};
   std::vector<double> cost(W);
   for (int w = 0; w < W; ++w) cost[w] = wave_step_cost(c->P, c->cfg.gr_c > 0, w);
   plan_windows(cost, c->chunk, slots, PLAN_Q, hw, hs, c->plan_off);
