@@ -9,6 +9,8 @@ ROOT = os.path.dirname(PKG)
 SRC = os.path.join(PKG, "csrc", "wh.hip")
 PAIR_SRC = os.path.join(PKG, "csrc", "wh_pair_step.hip")
 WIDE_SRC = os.path.join(PKG, "csrc", "wh_wide_step.hip")
+WIDE_JACOBI_SRC = os.path.join(PKG, "csrc", "wh_wide_jacobi.hip")
+WIDE_ADJOINT_SRC = os.path.join(PKG, "csrc", "wh_wide_adjoint.hip")
 LIB = os.path.join(PKG, "libwh.so")
 ARCH = os.environ.get("WH_OFFLOAD_ARCH", "gfx950")
 
@@ -25,8 +27,13 @@ FLAGS = [
 # wavefronts per SIMD (three with the default schedule), it measured 1.6-2.4%
 # faster on 65536 eight-planet systems with GR, while the one-planet and split
 # kernels in wh.hip, one wavefront per SIMD in their launches, measured
-# slower with it.
-PAIR_FLAGS = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+# slower with it.  So are the four-lanes-per-planet kernels in democratic
+# heliocentric coordinates (us per step, default and max-ilp: one system 0.690
+# and 0.639, 1024 systems in the split packing 0.780 and 0.668, 2048 systems one
+# planet per lane 0.776 and 0.766; forward and back through 1000 steps of 1024
+# systems 1.59 and 1.52 ms, the reverse-mode kernel alone), while in Jacobi coordinates the default leads
+# (3000 systems of two to four planets 0.745 and 0.830).
+ILP_FLAGS = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 
 
 PROBE_SRC = os.path.join(PKG, "csrc", "fp64_issue_probe.hip")
@@ -46,12 +53,13 @@ def _hipcc(cmd, out, verbose):
 
 
 def build(verbose: bool = False, extra=()) -> str:
-    # three translation units compiled side by side, then linked into one
+    # five translation units compiled side by side, then linked into one
     # shared library (each object carries its own gfx950 code object)
     cflags = [f for f in FLAGS if f != "-shared"] + list(extra)
     with tempfile.TemporaryDirectory() as tmp:
         jobs = []
-        for src, more in ((SRC, []), (PAIR_SRC, PAIR_FLAGS), (WIDE_SRC, [])):
+        for src, more in ((SRC, []), (PAIR_SRC, ILP_FLAGS), (WIDE_SRC, ILP_FLAGS),
+                          (WIDE_JACOBI_SRC, []), (WIDE_ADJOINT_SRC, ILP_FLAGS)):
             obj = os.path.join(tmp, os.path.basename(src) + ".o")
             # a fixed compilation-unit id: the default one hashes the
             # temporary object path, which would make every build differ

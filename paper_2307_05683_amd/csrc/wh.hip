@@ -1246,27 +1246,6 @@ __global__ __launch_bounds__(256) void k_to_jacobi(StepParams p) {
 // segment k - 1, is recorded by other wavefronts of the same launch into the
 // second of two segment tapes.
 constexpr int TAPE_ROWS = WH_TAPE_ROWS;
-struct AdjParams {
-  StepParams sp;
-  const double* ck;    // k_adj_init: the final checkpoint
-  double* tape;        // tape of the segment being swept
-  double* grad;        // adjoint state
-  const double* gQ_T;  // caller layout [S*8*3]
-  const double* gV_T;
-  double* gQ_0;
-  double* gV_0;
-  double* gm;          // [S*8]
-  double* gm0;         // [S]
-  int n_seg;           // steps of the segment being swept
-  int first_synced;    // it starts from the synchronized initial state
-  int sweep_waves;     // wavefronts of the sweeping role (0: the launch only records)
-  int wide_waves;      // wavefronts of each role with four lanes per planet (0: a lane per planet)
-  const double* ck_rec;  // recording role: checkpoint of the segment to record,
-  double* tape_rec;      // the tape to fill,
-  int n_rec;             // its steps,
-  int rec_first_synced;  // and whether it starts from the synchronized initial state
-};
-
 __device__ __forceinline__ void load_ck(const double* ck, int ns, int slot, Lane& L) {
   L.qx = ck[slot]; L.qy = ck[ns + slot]; L.qz = ck[2 * ns + slot];
   L.vx = ck[3 * ns + slot]; L.vy = ck[4 * ns + slot]; L.vz = ck[5 * ns + slot];
@@ -1856,36 +1835,13 @@ template <bool GR, int SCH, bool FIN> __global__ __launch_bounds__(256) void k_a
 }
 
 // Waves [0, sweep_waves) sweep one segment, the waves after them record the
-// previous segment; each role covers the packing's waves once.  Contexts whose
-// step runs with four lanes per planet record (the same bits as the step,
-// which recording repeats) and sweep in that form too.
+// previous segment; each role covers the packing's waves once.
 template <bool GR, bool SPLIT, int SCH, bool FIN> __global__ __launch_bounds__(64) void k_adj_segment(AdjParams q) {
-  __shared__ double lds[WIDE_ADJ_LDS];
   const StepParams& p = q.sp;
   const int lane = threadIdx.x;
   int wave = (int)blockIdx.x;
   const bool sweep = !FIN && wave < q.sweep_waves;
   if (!sweep) wave -= q.sweep_waves;
-  const int ww = q.wide_waves;
-  if (ww > 0) {
-    if (wave >= ww) return;
-    if (sweep) {
-      const bool first = q.first_synced != 0;
-      if (SPLIT) wide_sweep<8, GR, SCH, 1>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
-      else if (wave < 4 * p.w1) wide_sweep<1, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
-      else if (wave < 4 * p.w2) wide_sweep<2, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
-      else if (wave < 4 * p.w4) wide_sweep<4, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
-      else wide_sweep<8, GR, SCH, 0>(p, q.grad, q.tape, ww, q.n_seg, first, wave, lds, lane);
-    } else {
-      const bool first = q.rec_first_synced != 0;
-      if (SPLIT) wide_record<8, GR, SCH, 1, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
-      else if (wave < 4 * p.w1) wide_record<1, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
-      else if (wave < 4 * p.w2) wide_record<2, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
-      else if (wave < 4 * p.w4) wide_record<4, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
-      else wide_record<8, GR, SCH, 0, FIN>(p, q.ck_rec, q.tape_rec, ww, q.n_rec, first, wave, lds, lane);
-    }
-    return;
-  }
   if (wave >= p.w8) return;
   const int slot = wave * 64 + lane;
   if (SPLIT) {
@@ -3028,7 +2984,7 @@ void launch_wide(const wh_ctx* c, const StepParams& p, hipStream_t st) {
 // wavefronts (four times the one-planet packing's, twice the split packing's)
 // are no more than the GPU has SIMDs: there the wavefront's own instructions
 // set the time, beyond it the sum of all.  Eight-planet systems without GR, us
-// per step with and without it: one system 0.66 and 0.95 (split packing 0.67
+// per step with and without it: one system 0.66 and 0.95 (split packing 0.64
 // and 0.78), 2048 systems, a wavefront per SIMD, 0.74 and 0.97 (0.77 and 0.80);
 // at 3072, 1.5 per SIMD, it would take 1.12 against 0.96.  Four planets: 4096
 // systems 0.65 and 0.75, 8192 systems 1.06 and 0.78; two planets: 8192 systems
@@ -3287,6 +3243,11 @@ void launch_adj_segment(const wh_ctx* c, const AdjParams& q, int record_waves, h
     return;
   }
   const dim3 grid(q.sweep_waves + (record_waves > 0 && q.wide_waves > 0 ? q.wide_waves : record_waves)), block(64);
+  if (q.wide_waves > 0) {
+    if (c->P.split) hipLaunchKernelGGL((k_adj_wide<GR, true, SCH, FIN>), grid, block, 0, st, q);
+    else hipLaunchKernelGGL((k_adj_wide<GR, false, SCH, FIN>), grid, block, 0, st, q);
+    return;
+  }
   if (c->P.pair) hipLaunchKernelGGL((k_adj_segment_pair<GR, SCH, FIN>), grid, block, 0, st, q);
   else if (c->P.split) hipLaunchKernelGGL((k_adj_segment<GR, true, SCH, FIN>), grid, block, 0, st, q);
   else hipLaunchKernelGGL((k_adj_segment<GR, false, SCH, FIN>), grid, block, 0, st, q);

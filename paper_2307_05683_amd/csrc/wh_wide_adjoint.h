@@ -21,6 +21,28 @@ namespace wh {
 constexpr int WIDE_ADJ_LDS = 512;    // doubles of LDS per wavefront
 constexpr int WIDE_TAPE = wh_host::WH_TAPE_ROWS * WIDE_SLOTS;   // doubles per wavefront and step
 
+// Launch parameters of the reverse pass.
+struct AdjParams {
+  StepParams sp;
+  const double* ck;    // k_adj_init: the final checkpoint
+  double* tape;        // tape of the segment being swept
+  double* grad;        // adjoint state
+  const double* gQ_T;  // caller layout [S*8*3]
+  const double* gV_T;
+  double* gQ_0;
+  double* gV_0;
+  double* gm;          // [S*8]
+  double* gm0;         // [S]
+  int n_seg;           // steps of the segment being swept
+  int first_synced;    // it starts from the synchronized initial state
+  int sweep_waves;     // wavefronts of the sweeping role (0: the launch only records)
+  int wide_waves;      // wavefronts of each role with four lanes per planet (0: a lane per planet)
+  const double* ck_rec;  // recording role: checkpoint of the segment to record,
+  double* tape_rec;      // the tape to fill,
+  int n_rec;             // its steps,
+  int rec_first_synced;  // and whether it starts from the synchronized initial state
+};
+
 // Recording (adj_record_lane): the checkpoint's state through n_rec steps.
 // Lanes 0..2 of a planet write the rows of their component, lane 3 the
 // anomaly.  FIN: the run's last segment, stored as the context's state at its
@@ -319,5 +341,11 @@ __device__ __forceinline__ void wide_sweep(const StepParams& p, double* grad, co
     wide_put<STORAGE>(gs + (size_t)7 * ns, g.m0);
   }
 }
+
+// The kernel of reverse mode in this form (k_adj_segment's counterpart), defined
+// and instantiated in wh_wide_adjoint.hip: wavefronts [0, sweep_waves) sweep one
+// segment, the following ones record the previous one (the same bits as the
+// step, which recording repeats).
+template <bool GR, bool SPLIT, int SCH, bool FIN> __global__ __launch_bounds__(64) void k_adj_wide(AdjParams q);
 
 }  // namespace wh

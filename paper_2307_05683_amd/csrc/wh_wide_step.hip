@@ -1,29 +1,8 @@
-// The step kernel of small ensembles (four lanes per planet, wh_wide.h): a
-// translation unit of its own, as the pair layout's, so that the library's
-// kernels compile side by side.
-#include "wh_wide.h"
+// The step kernel of small ensembles (four lanes per planet, wh_wide.h), DHC: a
+// translation unit of its own, as the pair layout's, for its schedule (build.py).
+#include "wh_wide_kernel.h"
 
 namespace wh {
-
-template <bool GR, int SCHEME, int KC, int STORAGE, bool JAC>
-__global__ __launch_bounds__(256) void k_step_wide(StepParams p) {
-  __shared__ double lds[4 * WIDE_LDS];
-  const int lane = threadIdx.x & 63, wb = threadIdx.x >> 6;
-  double* block = lds + wb * WIDE_LDS;
-  // wavefront of the launch, then of the packing (4 per wave of 64 slots, 2
-  // per wave of the split packing)
-  const int k = (int)(blockIdx.x * (blockDim.x >> 6)) + wb;
-  if constexpr (STORAGE == 1) {
-    if (k < 2 * p.w8) wide_group<8, GR, SCHEME, KC, 1, false>(p, k, block, lane);
-    return;
-  }
-  const int w = 4 * p.wave0 + k;
-  if (w >= 4 * p.w8) return;
-  if (w < 4 * p.w1) wide_group<1, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
-  else if (w < 4 * p.w2) wide_group<2, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
-  else if (w < 4 * p.w4) wide_group<4, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
-  else wide_group<8, GR, SCHEME, KC, 0, JAC>(p, w, block, lane);
-}
 
 #define WH_WIDE(STORAGE)                                                     \
   template __global__ void k_step_wide<false, WH_DKD, 0, STORAGE>(StepParams); \
@@ -38,11 +17,5 @@ __global__ __launch_bounds__(256) void k_step_wide(StepParams p) {
 WH_WIDE(0);
 WH_WIDE(1);
 #undef WH_WIDE
-template __global__ void k_step_wide<false, WH_DKD, 0, 0, true>(StepParams);
-template __global__ void k_step_wide<true, WH_DKD, 0, 0, true>(StepParams);
-template __global__ void k_step_wide<false, WH_KDK, 0, 0, true>(StepParams);
-template __global__ void k_step_wide<true, WH_KDK, 0, 0, true>(StepParams);
-template __global__ void k_step_wide<false, SCHEME_SABA, 0, 0, true>(StepParams);
-template __global__ void k_step_wide<true, SCHEME_SABA, 0, 0, true>(StepParams);
 
 }  // namespace wh
