@@ -3009,38 +3009,6 @@ wh_status choose_wide(wh_ctx* c) {
   return WH_OK;
 }
 
-// Even shares of n_steps over bins of the launch, for DHC with the paper's Kepler
-// counts in the one-planet and mixed packings; false if there is no such cut.
-// A slice takes some 8 us beyond its steps, which 64 steps outweigh.
-bool even_form(const wh_ctx* c, int bins, int n_steps, EvenShare& e) {
-  const Packing& P = c->P;
-  if (P.pair || P.split || P.serial || c->exchange != WH_EXCH_DPP || c->cfg.coords != WH_COORDS_DHC ||
-      c->cfg.kepler_counts != 0)
-    return false;
-  const int w[6] = {0, P.w1, P.w2, P.w4, P.mixed ? P.wm : P.w8, P.w8};
-  for (int g = 0; g < 6; ++g) e.first[g] = w[g];
-  for (int g = 0; g < 5; ++g) e.cost[g] = w[g + 1] > w[g] ? (int)wave_step_cost(P, c->cfg.gr_c > 0, w[g]) : 1;
-  e.bins = bins;
-  e.steps = n_steps;
-  const int64_t kicks = (int64_t)n_steps * (c->cfg.scheme >= WH_SABA2 ? c->cfg.scheme : 1);
-  e.slices = even_slices(e, (int)std::min<int64_t>(kicks / 64, 32));
-  return e.slices > 0;
-}
-// When an unbalanced launch takes even shares.  W waves put ceil(W / SIMDs) on
-// the busiest SIMD, whose time per step (eight-planet waves, us) is 1.04, 1.87,
-// 2.67 and 3.66 for one to four.  With a bin per SIMD an average
-// load of L eight-planet waves takes 1.04 L, with two 0.94 L, and each slice
-// some 8 us.  At 300 steps: L = 1.22 (10000 systems) 1.91 -> 1.45 us per step, 1.5
-// 1.87 -> 1.64, 1.71 1.87 -> 1.78, 2.0 1.96 -> 2.10; two bins per SIMD: 2.44
-// (20000) 2.67 -> 2.49, 3.06 (40011 systems of one to eight) 3.55 -> 3.21, 3.66
-// 3.66 -> 3.67; at 1000 steps L = 1.2 (9900 systems) 1.75 -> 1.20.  Beyond four
-// waves per SIMD the hardware's own dispatch evens the load out.
-bool choose_even(const wh_ctx* c, int n_steps, EvenShare& e) {
-  const int busiest = (c->P.nwaves + c->simds - 1) / c->simds;
-  if (busiest < 2 || busiest > 4 || !even_form(c, busiest == 2 ? c->simds : 2 * c->simds, n_steps, e)) return false;
-  const double load = even_total(e) / ((double)c->simds * *std::max_element(e.cost, e.cost + 5));
-  return load <= (busiest == 2 ? 1.65 : busiest == 3 ? 2.6 : 3.4);
-}
 void launch_even(const wh_ctx* c, const StepParams& p, EvenShare e, hipStream_t st) {
   const bool gr = c->cfg.gr_c > 0, dkd = c->cfg.scheme == WH_DKD;
   const dim3 grid((e.bins + 3) / 4), block(256);
@@ -3062,7 +3030,7 @@ void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
   StepParams p = step_params(c, n_steps);
   EvenShare e{};
   if (c->wide_waves > 0) launch_wide(c, p, st);
-  else if (choose_even(c, n_steps, e)) launch_even(c, p, e, st);
+  else if (choose_even(c->P, c->cfg, c->simds, n_steps, e)) launch_even(c, p, e, st);
   else launch_step_kernel(c, p, c->P.nwaves, st);
 }
 
@@ -3102,7 +3070,7 @@ wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
   if (k < 1) return WH_OK;
   const int slots = k * simds;
   if (W <= slots || W > 16 * slots) return WH_OK;
-  if ((k == 1 || !c->P.mixed || c->P.wm == c->P.w8) && even_form(c, slots, c->chunk, c->even)) {
+  if ((k == 1 || !c->P.mixed || c->P.wm == c->P.w8) && even_form(c->P, c->cfg, slots, c->chunk, c->even)) {
     c->plan_slots = slots;
     return WH_OK;
   }

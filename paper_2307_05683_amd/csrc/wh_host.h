@@ -534,12 +534,14 @@ inline void plan_windows(const std::vector<double>& cost, int R, int slots, int 
 
 // Even shares of a launch (McNaughton's wrap-around rule).  The one-planet
 // packings' waves of one group size cost the same, so laying all waves end to
-// end by cost and cutting the line into `bins` equal parts gives every bin the
-// same work.  A cut wave runs its first steps at the start of the lower bin
-// and the others at the end of the upper one; `slices` launches cut the bins'
-// time, and where no wave is longer than a bin less a slice (even_slices), one
-// of those cuts lies between the two parts.  Whole numbers below 2^52 in
-// double precision: exact.
+// end by their cost times the steps and cutting the line into `bins` equal
+// parts gives every bin the same work.  A cut wave runs its first steps at the
+// start of the lower bin and the others at the end of the upper one; `slices`
+// launches cut the bins' time, and where no wave is longer than a bin less a
+// slice (even_slices), one of those cuts lies between the two parts.  Bins end
+// on whole units of the line and a cut wave is cut on a step, so a bin's time
+// is off by less than one step at either end, however many steps there are.
+// Whole numbers below 2^52 in double precision: exact.
 #ifdef __HIPCC__
 #define WH_HD __host__ __device__
 #else
@@ -594,12 +596,12 @@ WH_HD inline int even_wave_at(const EvenShare& e, double x) {
 // Its wave, and how many of its steps fall into the slice; false: there is no
 // such piece.
 WH_HD inline bool even_piece(const EvenShare& e, int bin, int i, int& wave, int& steps) {
-  const double C = even_total(e), R = e.steps;
-  const double x0 = even_div(bin * C, e.bins), x1 = even_div((bin + 1) * C, e.bins);
-  const int tail = even_wave_at(e, x0), head = even_wave_at(e, x1);
+  const double R = e.steps, T = even_total(e) * R;
+  const double x0 = even_div(bin * T, e.bins), x1 = even_div((bin + 1) * T, e.bins);
+  const int tail = even_wave_at(e, even_div(x0, R)), head = even_wave_at(e, even_div(x1, R));
   int ct, ch, cost, dummy;
-  const double off_t = x0 - even_start(e, tail, ct), off_h = x1 - even_start(e, head, ch);
-  const double head_steps = even_div(off_h * R, ch), tail_steps = off_t > 0.0 ? R - even_div(off_t * R, ct) : 0.0;
+  const double off_t = x0 - even_start(e, tail, ct) * R, off_h = x1 - even_start(e, head, ch) * R;
+  const double head_steps = even_div(off_h, ch), tail_steps = off_t > 0.0 ? R - even_div(off_t, ct) : 0.0;
   const int from = tail + (off_t > 0.0 ? 1 : 0), whole = head - from;
   if (i > whole + 1) return false;
   wave = i == 0 ? head : i <= whole ? from + i - 1 : tail;
@@ -608,7 +610,7 @@ WH_HD inline bool even_piece(const EvenShare& e, int bin, int i, int& wave, int&
   if (!(n > 0.0)) return true;
   const double start = even_start(e, wave, cost), line0 = even_start(e, from, dummy);
   const double at = i == 0 ? 0.0 : head_steps * ch + R * ((i <= whole ? start : even_start(e, head, dummy)) - line0);
-  const double T = C * R, m = (double)e.bins * e.slices;
+  const double m = (double)e.bins * e.slices;
   double done = even_div(even_div(e.slice * T, m) - at, cost), end = even_div(even_div((e.slice + 1) * T, m) - at, cost);
   done = done < 0.0 ? 0.0 : done < n ? done : n;
   end = e.slice + 1 == e.slices ? n : end < 0.0 ? 0.0 : end < n ? end : n;
@@ -616,9 +618,14 @@ WH_HD inline bool even_piece(const EvenShare& e, int bin, int i, int& wave, int&
   return true;
 }
 // Slices such that one of their cuts lies between the two parts of any cut
-// wave, whose time is at most a bin's less a slice's (and four steps, for the
-// roundings); 0 if that would take more than `most` or more pieces than there
-// is room for.
+// wave; 0 if that would take more than `most` or more pieces than there is room
+// for.  In units of the line, with c the heaviest step: a wave of R steps cut
+// after h of them is busy in the lower bin until h c and in the upper bin from
+// at least bin R - 1 - c - (R - h) c (the bin's whole length, less one unit for
+// its ends and up to a step that its other cut wave gives away).  Between the
+// two lie bin R - R c - c - 1 units, and a slice's cut among them leaves a step
+// to the upper part, whose last step may end c after the bin: with slices of
+// at most bin R - R c - 4 c one always does.
 inline int even_slices(const EvenShare& e, int most) {
   const double bin = even_total(e) / e.bins;
   double c = 0.0, least = 1.0e300;
@@ -628,9 +635,41 @@ inline int even_slices(const EvenShare& e, int most) {
       least = std::min(least, (double)e.cost[g]);
     }
   const double room = bin * e.steps - c * (e.steps + 4.0);
-  if (room <= 0.0 || bin / least + 4.0 > EVEN_PIECES || even_total(e) * e.steps * e.bins > 4.0e15) return 0;
+  if (room <= 0.0 || bin / least + 4.0 > EVEN_PIECES || even_total(e) * e.steps * std::max(e.bins, most) > 4.0e15) return 0;
   const double m = std::ceil(bin * e.steps / room);
   return m <= most ? (int)std::max(m, 2.0) : 0;
+}
+
+// Even shares of n_steps over bins of the launch, for DHC with the paper's Kepler
+// counts in the one-planet and mixed packings; false if there is no such cut.
+// A slice takes some 8 us beyond its steps, which 64 steps outweigh.
+inline bool even_form(const Packing& P, const wh_config& cfg, int bins, int n_steps, EvenShare& e) {
+  if (P.pair || P.split || P.serial || cfg.exchange == WH_EXCH_LDS || cfg.coords != WH_COORDS_DHC ||
+      cfg.kepler_counts != 0)
+    return false;
+  const int w[6] = {0, P.w1, P.w2, P.w4, P.mixed ? P.wm : P.w8, P.w8};
+  for (int g = 0; g < 6; ++g) e.first[g] = w[g];
+  for (int g = 0; g < 5; ++g) e.cost[g] = w[g + 1] > w[g] ? (int)wave_step_cost(P, cfg.gr_c > 0, w[g]) : 1;
+  e.bins = bins;
+  e.steps = n_steps;
+  const int64_t kicks = (int64_t)n_steps * (cfg.scheme >= WH_SABA2 ? cfg.scheme : 1);
+  e.slices = even_slices(e, (int)std::min<int64_t>(kicks / 64, 32));
+  return e.slices > 0;
+}
+// When an unbalanced launch takes even shares.  W waves put ceil(W / SIMDs) on
+// the busiest SIMD, whose time per step (eight-planet waves, us) is 1.04, 1.87,
+// 2.67 and 3.66 for one to four.  With a bin per SIMD an average
+// load of L eight-planet waves takes 1.04 L, with two 0.94 L, and each slice
+// some 8 us.  At 300 steps: L = 1.22 (10000 systems) 1.91 -> 1.45 us per step, 1.5
+// 1.87 -> 1.64, 1.71 1.87 -> 1.78, 2.0 1.96 -> 2.10; two bins per SIMD: 2.44
+// (20000) 2.67 -> 2.49, 3.06 (40011 systems of one to eight) 3.55 -> 3.21, 3.66
+// 3.66 -> 3.67; at 1000 steps L = 1.2 (9900 systems) 1.75 -> 1.20.  Beyond four
+// waves per SIMD the hardware's own dispatch evens the load out.
+inline bool choose_even(const Packing& P, const wh_config& cfg, int simds, int n_steps, EvenShare& e) {
+  const int busiest = (P.nwaves + simds - 1) / simds;
+  if (busiest < 2 || busiest > 4 || !even_form(P, cfg, busiest == 2 ? simds : 2 * simds, n_steps, e)) return false;
+  const double load = even_total(e) / ((double)simds * *std::max_element(e.cost, e.cost + 5));
+  return load <= (busiest == 2 ? 1.65 : busiest == 3 ? 2.6 : 3.4);
 }
 
 }  // namespace wh_host
