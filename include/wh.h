@@ -256,14 +256,15 @@ int32_t wh_launch_windows(const wh_ctx* ctx, int32_t* slots);
  * initial synchronized state (Q0, V0), the planet masses and the star mass.
  * Usage: wh_init; wh_forward_ckpt(n, K, tape) (advances the context like
  * wh_step_n, stores a checkpoint every K steps in the tape and records the
- * last segment on the way);
+ * last segment on the way, unless the one-planet groups of this context step
+ * with WH_EXCH_LDS);
  * wh_adjoint_n(tape, dL/dQ_T, dL/dV_T) -> dL/dQ_0, dL/dV_0, dL/dm, dL/dm0.
- * The adjoint re-runs each earlier K-step segment from its checkpoint,
- * records the segment's per-step states and converged Kepler anomalies in the tape, and
- * sweeps it backwards with the hand-written transposed Jacobian of every
- * sub-step (the Kepler drift through the implicit function theorem); the
- * tape holds two segment buffers, so that segment k - 1 is recorded while
- * segment k is swept.  wh_tape_bytes gives the size: 96 B per lane slot per
+ * The adjoint re-runs each other K-step segment from its checkpoint with the
+ * DPP exchange, records the segment's per-step states and converged Kepler
+ * anomalies in the tape, and sweeps it backwards with the hand-written
+ * transposed Jacobian of every sub-step (the Kepler drift through the implicit
+ * function theorem); the tape holds two segment buffers, so that segment k - 1
+ * is recorded while segment k is swept.  wh_tape_bytes gives the size: 96 B per lane slot per
  * checkpoint plus 2 x 80 B per lane slot and step of a segment (2 x n x 80 B
  * for SABA_n, which records its n drift-kick units; ckpt_every x n must not
  * exceed 2^30).  Every scheme, packing and coordinate system: with WH_KDK a

@@ -3606,11 +3606,15 @@ wh_status wh_forward_ckpt(wh_ctx* c, int64_t n_steps, int64_t ckpt_every, void* 
   const int ns = c->P.ns;
   double* ck = (double*)((char*)tape + T.ck);
   dim3 blk(256), grd((ns + 255) / 256);
+  // the recording kernels run the DPP exchange: a context that steps with the
+  // other one in its one-planet groups steps its last segment too, and the
+  // reverse pass records it
+  const bool record = T.n_seg > 0 && (c->exchange == WH_EXCH_DPP || c->P.pair || c->P.split || c->P.serial);
   int64_t done = 0;
   for (int64_t k = 0; k <= T.n_seg; ++k) {
     hipLaunchKernelGGL(k_save_ck, grd, blk, 0, stream, c->st, ck + (size_t)k * 12 * ns, ns);
     if (k == T.n_seg) break;
-    if (k == T.n_seg - 1) {
+    if (record && k == T.n_seg - 1) {
       // the last segment is recorded on the way: the reverse pass starts by
       // sweeping it
       AdjParams q = adj_params(c);
@@ -3634,7 +3638,7 @@ wh_status wh_forward_ckpt(wh_ctx* c, int64_t n_steps, int64_t ckpt_every, void* 
   c->tape_steps = n_steps;
   c->tape_every = ckpt_every;
   c->tape_end = c->steps_done;
-  c->tape_last = T.n_seg > 0;
+  c->tape_last = record;
   return WH_OK;
 }
 
