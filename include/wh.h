@@ -133,7 +133,8 @@ typedef struct {
   double gr_c;         /* speed of light for the GR kick; <= 0 turns GR off */
   int32_t scheme;      /* WH_DKD, WH_KDK or WH_SABA2..4 */
   int32_t packing;     /* WH_PACK_* */
-  int32_t block_waves; /* wavefronts per workgroup: 1, 2 or 4 (0 = 1) */
+  int32_t block_waves; /* wavefronts per workgroup: 1, 2 or 4 (0 = 1); steps with four lanes per planet
+                          (the smallest ensembles) and even shares (see balance) choose their own */
   int32_t chunk_steps; /* steps per kernel launch (0 = 4096) */
   int32_t graph_launches; /* launches per replayed HIP graph (0 = 8, < 0 = no graph) */
   double z_max;        /* WH_F_ZMAX threshold on the Stumpff argument (0 = 1.0) */

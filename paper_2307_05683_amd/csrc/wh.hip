@@ -3009,21 +3009,23 @@ wh_status choose_wide(wh_ctx* c) {
   return WH_OK;
 }
 
-void launch_even(const wh_ctx* c, const StepParams& p, EvenShare e, hipStream_t st) {
+// The kernel of even shares for a context's configuration (even_form's), in
+// four-wave workgroups whatever block_waves says.
+const void* even_kernel(const wh_ctx* c) {
   const bool gr = c->cfg.gr_c > 0, dkd = c->cfg.scheme == WH_DKD;
-  const dim3 grid((e.bins + 3) / 4), block(256);
-  for (e.slice = 0; e.slice < e.slices; ++e.slice) {
-    if (c->P.mixed) {
-      if (dkd && gr) hipLaunchKernelGGL((k_step_even<true, WH_DKD, true>), grid, block, 0, st, p, e);
-      else if (dkd) hipLaunchKernelGGL((k_step_even<false, WH_DKD, true>), grid, block, 0, st, p, e);
-      else if (gr) hipLaunchKernelGGL((k_step_even<true, WH_KDK, true>), grid, block, 0, st, p, e);
-      else hipLaunchKernelGGL((k_step_even<false, WH_KDK, true>), grid, block, 0, st, p, e);
-    } else if (c->cfg.scheme >= WH_SABA2) hipLaunchKernelGGL((k_step_even<false, SCHEME_SABA>), grid, block, 0, st, p, e);
-    else if (dkd && gr) hipLaunchKernelGGL((k_step_even<true, WH_DKD>), grid, block, 0, st, p, e);
-    else if (dkd) hipLaunchKernelGGL((k_step_even<false, WH_DKD>), grid, block, 0, st, p, e);
-    else if (gr) hipLaunchKernelGGL((k_step_even<true, WH_KDK>), grid, block, 0, st, p, e);
-    else hipLaunchKernelGGL((k_step_even<false, WH_KDK>), grid, block, 0, st, p, e);
+  if (c->P.mixed) {
+    if (dkd) return gr ? (const void*)k_step_even<true, WH_DKD, true> : (const void*)k_step_even<false, WH_DKD, true>;
+    return gr ? (const void*)k_step_even<true, WH_KDK, true> : (const void*)k_step_even<false, WH_KDK, true>;
   }
+  if (c->cfg.scheme >= WH_SABA2) return (const void*)k_step_even<false, SCHEME_SABA>;
+  if (dkd) return gr ? (const void*)k_step_even<true, WH_DKD> : (const void*)k_step_even<false, WH_DKD>;
+  return gr ? (const void*)k_step_even<true, WH_KDK> : (const void*)k_step_even<false, WH_KDK>;
+}
+void launch_even(const wh_ctx* c, const StepParams& p, EvenShare e, hipStream_t st) {
+  StepParams q = p;
+  void* args[] = {(void*)&q, (void*)&e};
+  const dim3 grid((e.bins + 3) / 4), block(256);
+  for (e.slice = 0; e.slice < e.slices; ++e.slice) (void)hipLaunchKernel(even_kernel(c), grid, block, args, 0, st);
 }
 
 void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
@@ -3035,10 +3037,11 @@ void launch_step(const wh_ctx* c, int n_steps, hipStream_t st) {
 }
 
 // Balanced launch windows for one chunk (wh_config.balance): slots =
-// (resident waves per SIMD at the step kernel's occupancy) x (SIMDs), using at
-// most as many waves per SIMD as the packing has waves for.  The chunk runs as
-// even shares over the slots where there are any, else plan_windows (wh_host.h)
-// cuts it.  Chunks of 4096 steps, us per step in windows and in shares: 12000
+// (resident waves per SIMD at the occupancy of the kernel that runs) x (SIMDs),
+// using at most as many waves per SIMD as the packing has waves for.  The chunk
+// runs as even shares over the slots where there are any, else plan_windows
+// (wh_host.h) cuts it.  The two kernels may hold different numbers of waves:
+// with GR kick-drift-kick in the mixed packing three (157 registers) and four.  Chunks of 4096 steps, us per step in windows and in shares: 12000
 // systems of eight 1.46 and 1.42, 20000 2.26 and 2.18, 40000 4.36 and 4.30; 20000 systems
 // of two to six in the mixed packing 1.31 and 1.28.  With several waves of
 // shared groups on a SIMD the windows lead: 35000 such systems 2.03 and 2.05,
@@ -3052,26 +3055,28 @@ wh_status build_plan(wh_ctx* c, std::vector<int>& hw, std::vector<int>& hs) {
   hw.clear();
   hs.clear();
   if (c->cfg.balance != 1 || c->P.serial || c->wide_waves > 0) return WH_OK;
-  int dev = 0, ncu = 0, nb = 0;
+  const int W = c->P.nwaves, simds = c->simds;
   wh_status st;
-  if ((st = hip_check(hipGetDevice(&dev), "hipGetDevice")) ||
-      (st = hip_check(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev), "CU count")))
-    return st;
-  int bw;
+  int k = 0;
+  // wavefronts of a plan for a kernel in workgroups of bw waves; 0: no plan
+  auto slots_of = [&](const void* kernel, int bw, size_t smem, int& slots) {
+    int nb = 0;
+    const wh_status s = hip_check(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, 64 * bw, smem),
+                                  "occupancy query");
+    k = std::min(nb * bw / 4, W / simds);   // resident wavefronts per SIMD
+    slots = k * simds;
+    if (W <= slots || W > 16 * slots) slots = 0;
+    return s;
+  };
+  int bw, slots = 0, bins = 0;
   size_t smem;
   step_block_shape(c, bw, smem);
-  if ((st = hip_check(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, step_kernel(c), 64 * bw, smem),
-                      "occupancy query")))
-    return st;
-  const int simds = 4 * ncu;                 // CDNA: four SIMDs per compute unit
-  const int per_simd = nb * bw / 4;          // resident wavefronts per SIMD
-  const int W = c->P.nwaves;
-  const int k = std::min(per_simd, W / std::max(simds, 1));
-  if (k < 1) return WH_OK;
-  const int slots = k * simds;
-  if (W <= slots || W > 16 * slots) return WH_OK;
-  if ((k == 1 || !c->P.mixed || c->P.wm == c->P.w8) && even_form(c->P, c->cfg, slots, c->chunk, c->even)) {
-    c->plan_slots = slots;
+  if ((st = slots_of(step_kernel(c), bw, smem, slots))) return st;
+  if (slots == 0) return WH_OK;
+  if ((st = slots_of(even_kernel(c), 4, 0, bins))) return st;
+  if (bins > 0 && (k == 1 || !c->P.mixed || c->P.wm == c->P.w8) &&
+      even_form(c->P, c->cfg, bins, c->chunk, c->even)) {
+    c->plan_slots = bins;
     return WH_OK;
   }
   c->even = EvenShare{};

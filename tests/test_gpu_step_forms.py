@@ -116,3 +116,16 @@ def test_large_gradients_are_the_small_ones(packing, lo, hi, big, scheme, gr_c):
         x = x.reshape(30, -1)
         d = np.abs(x[idx] - y.reshape(big, -1)).max(axis=1)
         assert np.all(d <= 3e-11 * np.abs(x).max(axis=1)[idx])
+
+
+def test_balanced_shares_fit_the_kernel_that_runs_them():
+    """Kick-drift-kick with GR in the mixed packing: the kernel of even shares
+    holds three wavefronts per SIMD (157 registers), the packing's own kernel
+    four; a plan of 5001 wavefronts over four would run in two rounds."""
+    s = batch(40008, 8, 8, 65)
+    kw = dict(packing="mixed", scheme="kdk", gr_c=40.0, chunk_steps=CHUNK)
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    shares, w = run(s, [N], balance=1, **kw)
+    assert w[0] > 1 and w[1] == 3 * simds
+    plain, _ = run(s, [SHORT] * (N // SHORT) + [N % SHORT], **kw)
+    same(shares, plain)
