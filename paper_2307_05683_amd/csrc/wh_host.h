@@ -475,10 +475,13 @@ inline TapeLayout tape_layout(int ns, int64_t n_steps, int64_t every, int units)
 // (1024 one-size wavefronts: 0.662 / 0.692 / 0.791 of the 8-lane step for
 // 1, 2, 4 lanes without GR, 0.627 / 0.698 / 0.790 with; the instruction
 // counts, 293 / 326 / 372 / 478, had the 4-lane waves 1.6% too cheap).  Shared
-// groups: the cost that runs the uneven batch (16384 systems of 2 to 8 planets)
-// fastest in even shares: without GR 1.300 us per step at 543, 1.320 at 530 and
-// 1.331 at 570; with GR 1.465 at 626, 1.484 at 612, 1.494 at 598 and 1.480 at
-// 640.  Two planets per lane: VALU instructions per lane-step.
+// groups: their VALU instructions' ratio gives 543 and 598, their time alone 558
+// and 626, and of these the costs that run mixed batches fastest are taken.  In
+// even shares (16384 systems of 2 to 8 planets), without GR 1.300 us per step at
+// 543, 1.320 at 530 and 1.331 at 570; with GR 1.465 at 626, 1.484 at 612, 1.494
+// at 598 and 1.480 at 640.  In windows of 2048 steps with GR, at 598 and 626:
+// 30000 systems of 2 to 8 planets 5.39 and 5.30 ms, 35000 of 2 to 6 5.11 and
+// 5.03, 49152 of 1 to 8 7.57 and 7.54.  Two planets per lane: VALU instructions per lane-step.
 inline double wave_step_cost(const Packing& P, bool with_gr, int w) {
   const int gr = with_gr ? 1 : 0;
   if (P.split) return 1.0;
