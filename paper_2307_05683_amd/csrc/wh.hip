@@ -677,7 +677,7 @@ __device__ __forceinline__ void serial_kick_drift(SerialState<NP>& S, double* cl
   }
 }
 
-// The end of a launch: state and compensation to memory, the system's flags.
+// The end of a recorded run: state and compensation to memory, the system's flags.
 template <int NP>
 __device__ __forceinline__ void serial_end(const StepParams& p, const SerialState<NP>& S, double* cl, int base, int n,
                                            const KepDiag& dg) {
@@ -770,7 +770,28 @@ __device__ void step_serial(const StepParams& p, int base, int n, double* cl) {
       ti = dt;
     }
   }
-  serial_end<NP>(p, S, cl, base, n, dg);
+  // serial_end's body: called instead, it moves the loop's schedule (kick-
+  // drift-kick 0.8% slower, 200 steps of 65536 eight-planet systems 1589 and 1601 us)
+  int f = 0;
+  double* so = p.st;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const bool fin = __builtin_isfinite(S.qx[i]) && __builtin_isfinite(S.qy[i]) && __builtin_isfinite(S.qz[i]) &&
+                     __builtin_isfinite(S.vx[i]) && __builtin_isfinite(S.vy[i]) && __builtin_isfinite(S.vz[i]);
+    if (i < n && !fin) f |= WH_F_NONFINITE;
+    so[base + i] = S.qx[i];
+    so[ns + base + i] = S.qy[i];
+    so[2 * ns + base + i] = S.qz[i];
+    so[3 * ns + base + i] = S.vx[i];
+    so[4 * ns + base + i] = S.vy[i];
+    so[5 * ns + base + i] = S.vz[i];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) so[(7 + k) * ns + base + i] = comp_at(cl, k, i);
+  }
+  if (!(dg.bmin > 0.0)) f |= WH_F_HYPERBOLIC;
+  if (!(dg.zmax <= p.zlim)) f |= WH_F_ZMAX;
+  p.flags[sys] |= (uint32_t)f;
+  p.synced[sys] = 0;
 }
 
 // Dynamic LDS: SERIAL_LDS_PER_WAVE doubles per wave of the block.
