@@ -64,19 +64,38 @@ DEFAULT_PACKING = {"large8gr": "pair", "uneven2to8": "mixed", "uniform8": "split
 # Wavefronts per workgroup: four-wave workgroups put one wave of each
 # workgroup on each SIMD of a CU.
 DEFAULT_BLOCK_WAVES = {"large8gr": 1, "uneven2to8": 4, "uniform8": 4, "single8": 1, "adjoint8": 4}
-# Balanced launch windows (wh_config.balance) for the uneven batch: its
+# Balanced launches (wh_config.balance) for the uneven batch: its
 # one-planet-per-lane wavefronts of several costs (1315 with two systems
 # sharing the 8-lane groups of 5+3 and 6+2 planets, 1535 without) run in
-# windows of 1024 equal-work wavefronts (+15% over two planets per lane,
+# even shares over 1024 wavefronts (in windows, +15% over two planets per lane,
 # whose 769 heavy wavefronts leave a quarter of the SIMDs idle; the shared
-# groups add 6%).  The GR batch's 4096 pair wavefronts of one cost measured
-# the same with and without windows.
+# groups add 6%, the shares 1.5%).  The GR batch's 4096 pair wavefronts of one
+# cost measured the same with and without windows.
 DEFAULT_BALANCE = {"large8gr": 0, "uneven2to8": 1, "uniform8": 0, "single8": 0, "adjoint8": 0}
 KERNEL_NAME = {"pair": "k_step_pair (persistent step kernel, two planets per lane)",
                "split": "k_step_split (persistent step kernel, two lanes per planet)",
                "serial": "k_step_serial (persistent step kernel, one lane per system)",
                "mixed": "k_step_mixed (persistent step kernel, one planet per lane, two systems in some 8-lane "
                         "groups)"}
+KERNEL_EVEN = "k_step_even (persistent step kernel, even shares of a launch, one planet per lane%s)"
+KERNEL_WIDE = "k_step_wide (persistent step kernel, four lanes per planet)"
+
+
+def kernel_name(n_planets, packing, windows=1, exchange="auto", coords="dhc"):
+    """The step kernel that the library picks for a workload: four lanes per
+    planet while that leaves a SIMD to each wavefront, even shares for balanced
+    launches, else the packing's own."""
+    import torch
+    groups = packing in ("auto", "pow2", "g8")
+    if exchange != "lds" and (groups or packing == "split"):
+        sizes = [(n, n, 8) for n in range(1, 9)] if packing == "g8" else [(1, 1, 1), (2, 2, 2), (3, 4, 4), (5, 8, 8)]
+        waves = (-(-len(n_planets) // 4) * 2 if packing == "split" else
+                 4 * sum(-(-int(((n_planets >= a) & (n_planets <= b)).sum()) * g // 64) for a, b, g in sizes))
+        if waves <= 4 * torch.cuda.get_device_properties(0).multi_processor_count:
+            return KERNEL_WIDE
+    if windows > 1 and exchange != "lds" and coords == "dhc" and (groups or packing == "mixed"):
+        return KERNEL_EVEN % (", two systems in some 8-lane groups" if packing == "mixed" else "")
+    return KERNEL_NAME.get(packing, "k_step (persistent step kernel)")
 
 
 def parse():
@@ -296,7 +315,7 @@ def leg_uniform(dev, stream, chunk):
     return {"workload": WORKLOAD_TEXT["uniform8"], "packing": "split", "value": s.S * n * chunk / t,
             "unit": "system-steps/s", "steps": n * chunk, "avg_launch_ms": t * 1e3 / n,
             "frac": fl * chunk / (t / n) / 1e12 / FP64_PEAK_TFLOPS,
-            "kernel": KERNEL_NAME["split"]}
+            "kernel": kernel_name(s.n_planets, "split")}
 
 
 def leg_uneven(dev, stream, chunk):
@@ -345,7 +364,7 @@ def leg_uneven(dev, stream, chunk):
     return {"workload": WORKLOAD_TEXT["uneven2to8"], "packing": pk, "block_waves": bw, "balance": bal,
             "launches_per_chunk": windows, "value": fused,
             "unit": "system-steps/s", "steps": n * chunk, "avg_launch_ms": t * 1e3 / n,
-            "frac": fl * chunk / (t / n) / 1e12 / FP64_PEAK_TFLOPS, "kernel": KERNEL_NAME.get(pk, "k_step"),
+            "frac": fl * chunk / (t / n) / 1e12 / FP64_PEAK_TFLOPS, "kernel": kernel_name(s.n_planets, pk, windows),
             "plain_per_size": {"value": s.S * n_plain / tp, "steps": n_plain},
             "speedup_fused_over_plain": fused / (s.S * n_plain / tp),
             "per_size_persistent": {"value": s.S * chunk / ts, "steps": chunk},
@@ -575,7 +594,7 @@ def main():
             "traffic": None,
             "traffic_unit": "HBM bytes per bench step: one launch, or one chunk of balanced windows "
                             "(rocprofv3 FETCH_SIZE/WRITE_SIZE, copy-calibrated)",
-            "kernel": KERNEL_NAME.get(packing, "k_step (persistent step kernel)"),
+            "kernel": kernel_name(systems.n_planets, packing, windows, args.exchange, args.coords),
             "algorithmic_flops_per_launch": flops_step * chunk,
             "avg_launch_ms": avg_launch * 1e3,
             "launches": args.steps,
